@@ -25,8 +25,8 @@
  *    null stream). The caller keeps the buffers alive until the stream has
  *    passed the call.
  *  - Every configuration accumulates each output in one FP32 register, with
- *    fused multiply-add, taps in i-ascending then j-ascending order, starting
- *    from 0. Results are therefore bitwise identical across configurations,
+ *    fused multiply-add (plain or in a matrix instruction: the same rounding),
+ *    taps in i-ascending then j-ascending order, starting from 0. Results are therefore bitwise identical across configurations,
  *    batch and serving paths, and the reference kernel.
  *  - Filter sizes are limited to 1..63 per axis; out_h, out_w >= 1.
  */
@@ -63,7 +63,8 @@ typedef struct conv2d_config {
     int filter_in_const;  /* 1: filter in a __constant__ array, 0: const global pointer
                              (the analogue of read_only) */
     int unroll;           /* input-row loop unroll: 1, 2, 4, or 0 = full
-                             (the paper's tunable partial unroll, Section 3) */
+                             (the paper's tunable partial unroll, Section 3);
+                             other than 1, even tile sizes use the matrix cores */
 } conv2d_config;
 
 typedef struct conv2d_shape {

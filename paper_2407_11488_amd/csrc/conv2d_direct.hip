@@ -41,6 +41,9 @@
 //    it (TY*TX*FW FMAs per window in the steady state). Filter taps are wave
 //    uniform and are read with scalar loads, so each FMA is
 //    v_fmac_f32 acc, s_tap, v_in.
+//  * With an unroll other than 1 and tiles of whole 2 x 2 output blocks, most
+//    of those FMAs run on the matrix cores instead, at twice the rate and with
+//    the same bits (MatrixRows below).
 //  * Global reads use raw buffer loads: an out-of-range dword reads 0
 //    instead of faulting, so edge tiles need no clamping; outputs outside the
 //    image are simply not stored.
@@ -65,6 +68,24 @@ typedef u32 u32x2 __attribute__((ext_vector_type(2)));
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The CPU build of this file has no matrix instruction unless its harness
+// supplies one under the builtin's name (and says so).
+#if defined(__AMDGCN__) || defined(CONV_EMULATED_MFMA)
+#define CONV_HAVE_MFMA 1
+#else
+#define CONV_HAVE_MFMA 0
+#endif
+
+// At least two waves per SIMD on the matrix path: with more than 256 registers
+// to hand out, the compiler keeps the accumulators of matrix instructions in
+// the other half of the register file, where plain FMAs cannot reach them, and
+// moves each one out and back around every FMA.
+#if defined(__AMDGCN__)
+#define CONV_WAVES __attribute__((amdgpu_waves_per_eu(G1::MATRIX ? 2 : 1)))
+#else
+#define CONV_WAVES
+#endif
 
 static constexpr int gcd4(int t) { return (t % 4 == 0) ? 4 : ((t % 2 == 0) ? 2 : 1); }
 static constexpr int min_(int a, int b) { return a < b ? a : b; }
@@ -95,6 +116,13 @@ struct Geo {
     static constexpr int LDS_PITCH = (LDS_PITCH0 % 32 == 0) ? LDS_PITCH0 + 4 : LDS_PITCH0;
     static constexpr int LDS_FLOATS = LDS ? LDS_ROWS * LDS_PITCH : 4;
     static constexpr int ROW_UNROLL = UNROLL == 0 ? NROWS : UNROLL;   // 0 = the whole row loop
+    // Matrix path (see MatrixRows): whole waves, output tiles of whole 2 x 2
+    // blocks, a filter with interior taps, and a row loop that is not asked to
+    // stay rolled (unroll 1 keeps one row's plain FMAs as its body). From 3 x 3
+    // on it is never the slower one: 4 x (9 FMAs) there take 144 cycles plain
+    // and 4 * 8 + 20 * 4 = 112 here, 17 x 17 4624 and 2576.
+    static constexpr bool MATRIX = CONV_HAVE_MFMA && UNROLL != 1 && TX % 2 == 0 && TY % 2 == 0 && NT % 64 == 0 &&
+                                   FH >= 3 && FW >= 3;
 };
 
 // Filter taps: the module's __constant__ copy, or the filter pointer.
@@ -163,6 +191,150 @@ static __device__ __forceinline__ int xcd_remap(int id, int n_tiles)
     return xcd * q + min_(xcd, rem) + k;
 }
 
+#if CONV_HAVE_MFMA
+// The rows of a thread's tile on the matrix cores.
+//
+// v_mfma_f32_4x4x1_16b adds, in each of 16 blocks of 4 lanes, the product of a
+// 4-vector A and a 4-vector B to a 4 x 4 matrix; lane l of a block keeps
+// column l of it in 4 registers and supplies B[l]. So with B = one input value
+// of the lane's own window, the instruction is 4 FMAs of that value into 4
+// accumulators of the same lane, acc[m] += A[m] * w: the outputs of a 2 x 2
+// block (rows y, y+1, columns x, x+1) with the four taps
+// f[i - my][k - mx] that input value w[i][k] meets there, m = 2 my + mx. Every
+// such product is one the convolution needs where i is in [1, FH-1] and k in
+// [1, FW-1]; the rim of the (FH+1) x (FW+1) inputs of a 2 x 2 block stays on
+// plain FMAs, so that no product with a padding zero is added (an infinity in
+// the input reaches only the outputs it belongs to) and every output still
+// sums its taps one by one in the fixed order, in FMAs that round alike: the
+// bits are those of the plain path.
+//
+// A needs no broadcast code: one register holds the four taps of 16 columns k
+// (lane 4 q + m: column 1 + q), and the instruction's broadcast control
+// (cbsz 4, abid q) feeds block q's taps to all blocks. A filter row pair thus
+// costs one register per 16 columns, gathered from the filter by one load.
+//
+// 4 x 4 x 1 runs 256 FMAs in 8 cycles, a plain FMA 64 in 4: a 17 x 17 block
+// takes 256 * 8 + 132 * 4 = 2576 cycles against 1156 * 4 = 4624 (the two do
+// not overlap: a mix of both measured the sum of their times). Bound by these
+// issue cycles: at 4096 x 4096 / 17 x 17 they are 171 of the 184 thousand
+// cycles a CU is busy. Measured against the plain path's winners, 4096 x 4096:
+// 31 x 31 432 -> 256 us, 17 x 17 134.7 -> 88.1 (110 TFLOP/s), 15 x 15 106 ->
+// 73, 9 x 9 42 -> 34, 7 x 7 27.6 -> 25.8 and 3 x 3 21.8 -> 19.3 (both then near
+// what their 134 MB take: 28 us at the rate of a large copy).
+template <int FH, int FW, int TX, int TY, class G>
+struct MatrixRows {
+    static constexpr int NG = TX / 2, NP = TY / 2;    // 2 x 2 blocks along x and y
+    static constexpr int NA = (FW - 1 + 15) / 16;     // tap registers per filter row pair
+    // Rows in which every block row is inside the filter: [FIRST, LAST].
+    static constexpr int FIRST = 2 * NP - 1, LAST = FH - 1;
+    // With the row loop fully unrolled and few enough of them, all taps are
+    // loaded once, ahead of the tile (`held`); else each row loads its own.
+    static constexpr bool HOLD = G::ROW_UNROLL >= G::NROWS && NA * (FH - 1) <= 32;
+
+    f32x4 acc[NP][NG];
+    float held[HOLD ? FH - 1 : 1][NA];
+
+    // The taps of filter rows i (my = 0) and i - 1 (my = 1).
+    template <class Rsrc>
+    static __device__ __forceinline__ void taps(float (&a)[NA], Rsrc rf, u32 lane_off, int i)
+    {
+#pragma unroll
+        for (int n = 0; n < NA; ++n)
+            a[n] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 rf, (int)(lane_off + (u32)((i - 1) * FW + 16 * n) * 4u), 0, 0));
+    }
+
+    // Is block row p at an input row r that meets interior taps (r is a
+    // constant after unrolling, or any row of the steady range)?
+    static __device__ __forceinline__ constexpr bool inside(int p, int r) { return r - 2 * p >= 1 && r - 2 * p < FH; }
+
+    // The interior columns of input row r, for every block row inside.
+    template <bool STEADY, int N, int K>
+    __device__ __forceinline__ void columns(int r, const float (&a)[NP][NA], const float* w)
+    {
+        if constexpr (K < 16 && 16 * N + K < FW - 1) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if (STEADY || inside(p, r)) {
+#pragma unroll
+                    for (int g = 0; g < NG; ++g)
+                        acc[p][g] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[p][N], w[2 * g + 1 + 16 * N + K], acc[p][g],
+                                                                       4, K, 0);
+                }
+            columns<STEADY, N, K + 1>(r, a, w);
+        } else if constexpr (K == 16 && N + 1 < NA) {
+            columns<STEADY, N + 1, 0>(r, a, w);
+        }
+    }
+
+    // Block row p's first (MY = 0, filter row 0) or last input row (MY = 1,
+    // filter row FH - 1): one output row of the two, plain FMAs.
+    template <int MY>
+    __device__ __forceinline__ void rim(int p, const float* w, const float* __restrict__ ft)
+    {
+#pragma unroll
+        for (int j = 0; j < FW; ++j) {
+            const float fv = ft[(MY ? (FH - 1) * FW : 0) + j];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                acc[p][g][2 * MY] = __builtin_fmaf(w[2 * g + j], fv, acc[p][g][2 * MY]);
+                acc[p][g][2 * MY + 1] = __builtin_fmaf(w[2 * g + 1 + j], fv, acc[p][g][2 * MY + 1]);
+            }
+        }
+    }
+
+    // Column k = 0 (FIRSTCOL) or FW of block row p at its input row i.
+    template <bool FIRSTCOL>
+    __device__ __forceinline__ void side(int p, int i, const float* w, const float* __restrict__ ft)
+    {
+        constexpr int J = FIRSTCOL ? 0 : FW - 1, K = FIRSTCOL ? 0 : FW, X = FIRSTCOL ? 0 : 1;
+        const float f0 = ft[i * FW + J], f1 = ft[(i - 1) * FW + J];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            acc[p][g][X] = __builtin_fmaf(w[2 * g + K], f0, acc[p][g][X]);
+            acc[p][g][2 + X] = __builtin_fmaf(w[2 * g + K], f1, acc[p][g][2 + X]);
+        }
+    }
+
+    // Input row r (a constant after unrolling, unless STEADY) for every block
+    // row. The plain FMAs of a row come in one run, the matrix instructions in
+    // another, and the scheduler keeps them so: each change from one to the
+    // other and back costs about 6 cycles (14 cycles for one of each become
+    // 21 when they alternate).
+    template <bool STEADY, class Rsrc>
+    __device__ __forceinline__ void row(int r, const float* w, Rsrc rf, u32 lane_off, const float* __restrict__ ft)
+    {
+        constexpr int kFence = 0x4 | 0x10 | 0x80;   // scalar and memory instructions may cross, ALU ones not
+        float a[NP][NA];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int i = r - 2 * p;
+            if (STEADY || inside(p, r)) {
+                if constexpr (HOLD) {
+#pragma unroll
+                    for (int n = 0; n < NA; ++n)
+                        a[p][n] = held[i - 1][n];
+                } else {
+                    taps(a[p], rf, lane_off, i);
+                }
+                side<true>(p, i, w, ft);
+            } else if (i == 0) {
+                rim<0>(p, w, ft);
+            } else if (i == FH) {
+                rim<1>(p, w, ft);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(kFence);
+        columns<STEADY, 0, 0>(r, a, w);
+        __builtin_amdgcn_sched_barrier(kFence);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (STEADY || inside(p, r))
+                side<false>(p, r - 2 * p, w, ft);
+    }
+};
+#endif
+
 // One output tile of (BY*TY) x (BX*TX) at tile coordinates (tile_y, tile_x)
 // of an image. Every thread of the workgroup calls it (the LDS variant
 // contains a barrier). `lds` is the workgroup's LDS tile.
@@ -179,34 +351,138 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
     const u32 P = (u32)W + (FW - 1);
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(in, in_bytes);
 
+#if CONV_HAVE_MFMA
+    using M = MatrixRows<FH, FW, TX, TY, G>;
+    M m;
+    const u32 lane = threadIdx.x & 63u;
+    const u32 lane_off = ((1u - ((lane >> 1) & 1u)) * FW + (lane >> 2) + 1u - (lane & 1u)) * 4u;
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(filt, FH * FW * 4u);
+    if constexpr (G::MATRIX && M::HOLD) {
+#pragma unroll
+        for (int i = 1; i < FH; ++i)
+            M::taps(m.held[i - 1], rf, lane_off, i);
+    }
+#endif
+
     const float* lbase = lds;
     if constexpr (LDS) {
-        const u32 gx0 = (u32)tile_x * (BX * TX);
-        const u32 gy0 = (u32)tile_y * (BY * TY);
-        for (int c = (int)threadIdx.x; c < G::LDS_ROWS * G::LDS_CHUNKS; c += G::NT) {
-            const int rr = c / G::LDS_CHUNKS;
-            const int cc = (c - rr * G::LDS_CHUNKS) * VIN;
-            float v[VIN];
-            buffer_row<VIN, VIN>(v, rs, ((gy0 + rr) * P + gx0 + cc) * 4u);
+        // The halo tile, chunk by chunk in row order, NT chunks at a time. The
+        // loads of STAGE steps are in flight together (one exposed memory
+        // latency instead of one per step), and a step moves every thread by
+        // the same number of rows and chunks, so positions are only added up.
+        constexpr int STEPS = (G::LDS_ROWS * G::LDS_CHUNKS + G::NT - 1) / G::NT;
+        constexpr int STAGE = min_(STEPS, 8);
+        constexpr int DR = G::NT / G::LDS_CHUNKS, DC = G::NT % G::LDS_CHUNKS;
+        int c = (int)threadIdx.x;
+        int cc = c % G::LDS_CHUNKS, rr = c / G::LDS_CHUNKS;
+        u32 off = (((u32)tile_y * (BY * TY) + (u32)rr) * P + (u32)tile_x * (BX * TX) + (u32)(cc * VIN)) * 4u;
+        float* dst = lds + rr * G::LDS_PITCH + cc * VIN;
+        const u32 step = ((u32)DR * P + (u32)(DC * VIN)) * 4u;
+        const u32 wrap = (P - (u32)(G::LDS_CHUNKS * VIN)) * 4u;
+        auto advance = [&] {
+            c += G::NT;
+            cc += DC;
+            off += step;
+            dst += DR * G::LDS_PITCH + DC * VIN;
+            if (DC != 0 && cc >= G::LDS_CHUNKS) {
+                cc -= G::LDS_CHUNKS;
+                off += wrap;
+                dst += G::LDS_PITCH - G::LDS_CHUNKS * VIN;
+            }
+        };
+#pragma unroll 1
+        for (int s0 = 0; s0 < STEPS; s0 += STAGE) {
+            float v[STAGE][VIN];
+            float* to[STAGE];
 #pragma unroll
-            for (int m = 0; m < VIN; ++m)
-                lds[rr * G::LDS_PITCH + cc + m] = v[m];
+            for (int s = 0; s < STAGE; ++s) {
+                to[s] = c < G::LDS_ROWS * G::LDS_CHUNKS ? dst : nullptr;
+                buffer_row<VIN, VIN>(v[s], rs, off);
+                advance();
+            }
+#pragma unroll
+            for (int s = 0; s < STAGE; ++s) {
+                if (to[s]) {
+                    if constexpr (VIN == 4) {
+                        *(f32x4*)to[s] = f32x4{v[s][0], v[s][1], v[s][2], v[s][3]};
+                    } else {
+#pragma unroll
+                        for (int m = 0; m < VIN; ++m)
+                            to[s][m] = v[s][m];
+                    }
+                }
+            }
         }
         __syncthreads();
         lbase = lds + (ly * TY) * G::LDS_PITCH + lx * TX;
     }
 
+    const u32 off0 = ((u32)y0 * P + (u32)x0) * 4u;
+    float acc[TY][TX];
+
+#if CONV_HAVE_MFMA
+    if constexpr (G::MATRIX) {
+        // Matrix instructions take their A operand from lanes that may lie
+        // outside the image, so a wave computes with all of its lanes or not
+        // at all; what outside lanes read is in range or zero, and unused.
+        if (__builtin_amdgcn_ballot_w64(x0 < W && y0 < H) == 0)
+            return;
+#pragma unroll
+        for (int p = 0; p < M::NP; ++p)
+#pragma unroll
+            for (int g = 0; g < M::NG; ++g)
+                m.acc[p][g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        auto window = [&](float* w, int r) {
+            if constexpr (LDS)
+                lds_row<G::WVEC, G::WIN_PAD>(w, lbase + r * G::LDS_PITCH);
+            else
+                buffer_row<G::WVEC, G::WIN_PAD>(w, rs, off0 + (u32)r * P * 4u);
+        };
+        if constexpr (M::FIRST <= M::LAST && G::ROW_UNROLL < G::NROWS) {
+#pragma unroll
+            for (int r = 0; r < M::FIRST; ++r) {
+                float w[G::WIN_PAD];
+                window(w, r);
+                m.template row<false>(r, w, rf, lane_off, TAPS);
+            }
+#pragma unroll G::ROW_UNROLL
+            for (int r = M::FIRST; r <= M::LAST; ++r) {
+                float w[G::WIN_PAD];
+                window(w, r);
+                m.template row<true>(r, w, rf, lane_off, TAPS);
+            }
+#pragma unroll
+            for (int r = M::LAST + 1; r < G::NROWS; ++r) {
+                float w[G::WIN_PAD];
+                window(w, r);
+                m.template row<false>(r, w, rf, lane_off, TAPS);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < G::NROWS; ++r) {
+                float w[G::WIN_PAD];
+                window(w, r);
+                m.template row<false>(r, w, rf, lane_off, TAPS);
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < TY; ++o)
+#pragma unroll
+            for (int k = 0; k < TX; ++k)
+                acc[o][k] = m.acc[o / 2][k / 2][2 * (o & 1) + (k & 1)];
+        if (x0 >= W || y0 >= H)
+            return;
+    } else
+#endif
+    {
     if (x0 >= W || y0 >= H)
         return;
 
-    float acc[TY][TX];
 #pragma unroll
     for (int o = 0; o < TY; ++o)
 #pragma unroll
         for (int k = 0; k < TX; ++k)
             acc[o][k] = 0.0f;
-
-    const u32 off0 = ((u32)y0 * P + (u32)x0) * 4u;
 
 #pragma unroll G::ROW_UNROLL
     for (int r = 0; r < G::NROWS; ++r) {
@@ -228,6 +504,7 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
                 }
             }
         }
+    }
     }
 
 #pragma unroll
@@ -261,7 +538,7 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
 #if CONV_BATCH == 0
 // One image: one workgroup per tile, tiles_x * tiles_y = n_tiles workgroups.
 using G1 = Geo<CONV_FH, CONV_FW, CONV_BX, CONV_BY, CONV_TX, CONV_TY, CONV_USE_LDS, CONV_UNROLL, CONV_VIN, CONV_VOUT>;
-extern "C" __global__ void __launch_bounds__(G1::NT)
+extern "C" __global__ void __launch_bounds__(G1::NT) CONV_WAVES
 CONV_NAME(const float* __restrict__ in, const float* __restrict__ filt,
           float* __restrict__ out, int H, int W, int tiles_x, int n_tiles, u32 in_bytes)
 {
@@ -303,7 +580,7 @@ static __device__ __forceinline__ const ConvDesc* tile_desc(const ConvDesc* __re
 // workgroup id mod 8) form one contiguous range, shared out by stride among
 // that XCD's workgroups; owner[t] names the problem of tile t.
 using G1 = Geo<CONV_FH, CONV_FW, CONV_BX, CONV_BY, CONV_TX, CONV_TY, CONV_USE_LDS, CONV_UNROLL, CONV_VIN, CONV_VOUT>;
-extern "C" __global__ void __launch_bounds__(G1::NT)
+extern "C" __global__ void __launch_bounds__(G1::NT) CONV_WAVES
 CONV_NAME(const ConvDesc* __restrict__ descs, const unsigned short* __restrict__ owner, int total_tiles)
 {
     __shared__ __attribute__((aligned(16))) float lds[G1::LDS_FLOATS];
