@@ -228,8 +228,10 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * configuration form a group, run as one kernel over the group's tiles (a
  * workgroup per tile, the tiles of each image in row order, XCD-contiguous
  * runs). The
- * groups are parallel branches of one graph captured at plan time. Results
- * are bitwise identical to conv2d_run / conv2d_reference on the same data.
+ * groups are parallel branches of one graph captured at plan time; a batch too
+ * small to pay for the graph's launch has its kernels launched one after
+ * another. Results are bitwise identical to conv2d_run / conv2d_reference on
+ * the same data.
  * A batch plan must not run on two streams at once (its descriptor table is
  * shared); runs on one stream are ordered. Each input is limited to 2 GiB. */
 

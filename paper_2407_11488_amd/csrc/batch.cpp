@@ -4,9 +4,10 @@
 // group gets the tuned configuration of its filter size and one
 // kernel that walks the group's tile list; the problems are described in
 // device memory (pointers, sizes, first tile), so the graph is captured once
-// at plan time, with the groups as parallel branches, and a run is one
-// hipGraphLaunch (after a small descriptor upload when the caller's pointers
-// changed since the last run).
+// at plan time, with the groups as parallel branches, and a run of a large
+// batch is one hipGraphLaunch (after a small descriptor upload when the
+// caller's pointers changed since the last run). A small batch's kernels are
+// launched one after another instead (launch_directly).
 #include <algorithm>
 #include <atomic>
 #include <climits>
@@ -61,6 +62,7 @@ struct conv2d_batch_s {
     bool copy_pending = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    bool direct = false;                 // small batch: see launch_directly
     std::mutex mu;
 };
 
@@ -83,6 +85,22 @@ static void batch_free(conv2d_batch_s* b)
 static int launch_group(const Group& g, hipStream_t st)
 {
     return launch_batch_kernel(g.mod, g.cfg, g.grid, g.a_desc, g.a_owner, g.a_total, st);
+}
+
+// Does this batch run faster as plain launches than as its graph? Launching
+// the graph costs the host about 13 us per branch (10-14 us measured for 2 to
+// 6 branches), a plain launch 3 to 4 us, and the GPU gets the work that much
+// later; against that, parallel branches fill the tails of each other's
+// kernels. Measured per run, graph and direct: 16 images up to 768 (6 kernels)
+// 81 and 36 us, 4 images up to 512 (2 kernels) 38 and 14 us, 40 images up to
+// 1024 (6 kernels) 81 and 54 us; 64 images up to 2048 (4 kernels, 13.4 GFLOP)
+// 211 and 215 us. The line is where the kernels take 25 us per branch, at the
+// 65 TFLOP/s the large batch reaches.
+static bool launch_directly(const conv2d_batch_s* b)
+{
+    double flops = 0;
+    for (const auto& s : b->shapes) flops += 2.0 * s.out_h * (double)s.out_w * s.filt_h * s.filt_w;
+    return flops / 65e12 < 25e-6 * (double)b->groups.size();
 }
 
 // Captures every group's kernel as a parallel branch of one graph.
@@ -318,6 +336,7 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     if (!(flags & CONV2D_BATCH_NO_GRAPH)) {
         rc = capture(b.get());
         if (rc) return rc;
+        b->direct = launch_directly(b.get());
     }
     *out = b.release();
     return CONV2D_OK;
@@ -369,7 +388,14 @@ extern "C" int conv2d_batch_run(conv2d_batch_t b, const float* const* d_in, cons
         b->copy_pending = true;
         b->uploaded = ptrs;
     }
-    if (b->exec) {
+    // A stream that is being captured records the kernels themselves (a graph
+    // launched into it runs at once and leaves the captured graph empty).
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (b->exec && !b->direct && hipStreamIsCapturing(st, &capturing) != hipSuccess) {
+        (void)hipGetLastError();
+        capturing = hipStreamCaptureStatusActive;
+    }
+    if (b->exec && !b->direct && capturing == hipStreamCaptureStatusNone) {
         hipError_t e = hipGraphLaunch(b->exec, st);
         if (e != hipSuccess) return fail(CONV2D_ELAUNCH, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
         return CONV2D_OK;
