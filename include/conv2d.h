@@ -166,17 +166,18 @@ int conv2d_cache_store(const char *path, const char *arch, conv2d_shape s,
  * tuned winner for this shape from the winners cache (env CONV2D_WINNERS,
  * else the tuned/winners.jsonl file beside this library), else the winner of
  * the same filter size for another shape (4096 x 4096 first, else the most
- * recent) when it is legal for this shape, else the default
- * configuration; the environment variable CONV2D_FORCE_CONFIG
- * ("bx,by,tx,ty,lds,const,unroll") overrides both. Compiles (or loads from the
- * code-object cache) and loads the module. The plan owns the module.
+ * recent) when it is legal for this shape, else the cache's entry for any
+ * shape, (-1, -1, 0, 0), else the default configuration (below 2^22 outputs
+ * the entry for any shape comes before the filter's); the environment
+ * variable CONV2D_FORCE_CONFIG ("bx,by,tx,ty,lds,const,unroll") overrides
+ * them all. Compiles (or loads from the code-object cache) and loads the module. The plan owns the module.
  * Source: Section 5 (the convolution benchmark kernel) with a point of the
  * Table 1 space; the formula is the one at the top of this header. */
 int conv2d_plan(conv2d_plan_t *plan, conv2d_shape s, const conv2d_config *cfg);
 
 /* The configuration a plan uses, and whether it came from the winners cache
  * (*tuned = 1; 3 when that entry was tuned with an older revision of the
- * kernel source; 4 when it is the same filter's winner for another shape),
+ * kernel source; 4 when it is an entry for another shape or for any shape),
  * was forced or given (2), or is the default (0).
  * Source: Table 1 (the parameters of the configuration). */
 int conv2d_plan_config(conv2d_plan_t plan, conv2d_config *cfg, int *tuned);
@@ -223,8 +224,9 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * whole-batch entry (0, 0, fh, fw) from conv2d_batch_tune, else its size
  * bucket's entry (0, b, fh, fw) (with CONV2D_BATCH_BY_SIZE the other way
  * round), else the winners cache entry for 4096x4096 with that filter, else
- * the most recent entry with that filter, else the default; the filter is
- * always read through its pointer. The problems sharing a filter size and
+ * the most recent entry with that filter, else the entry for any shape (before
+ * the filter's with CONV2D_BATCH_BY_SIZE up to 1536), else the default; the
+ * filter is always read through its pointer. The problems sharing a filter size and
  * configuration form a group, run as one kernel over the group's tiles (a
  * workgroup per tile, the tiles of each image in row order, XCD-contiguous
  * runs). The

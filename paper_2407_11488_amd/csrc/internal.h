@@ -212,5 +212,18 @@ int cache_store(const std::string& path, const std::string& arch, const conv2d_s
 // most recent entry of any shape with that filter size.
 int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
                         const conv2d_shape& prefer, conv2d_config* c);
+// The winners-cache shape of the configuration for any size and any filter: a
+// compromise over both, for shapes that have no better entry. It must be legal
+// for s.
+constexpr conv2d_shape kAnyShape{-1, -1, 0, 0};
+int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2d_shape& s, conv2d_config* c);
+// Outputs below which that entry is preferred to the winner of the filter at
+// another size. The shipped entry has 128 x 16 outputs a workgroup: up to
+// about 8 waves per SIMD of it. Winners at 4096 x 4096 have larger tiles that
+// leave CUs idle on smaller images: measured against it, a winner takes 1.0 to
+// 2.7 times as long up to 1400 x 1400 (31 x 31 on 512 x 512: 34.0 and 13.1 us,
+// 17 x 17 8.8 and 5.6), 0.97 to 1.08 at 2000 x 2000 and 0.93 to 1.0 at 2800 x
+// 2800.
+constexpr long long kSmallOutputs = 1ll << 22;
 
 }  // namespace conv2d

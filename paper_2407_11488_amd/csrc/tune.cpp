@@ -103,6 +103,15 @@ int cache_lookup_filter(const std::string& path, const std::string& arch, int fh
     return CONV2D_OK;
 }
 
+int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2d_shape& s, conv2d_config* c)
+{
+    conv2d_config any{};
+    int rc = cache_lookup(path, dev.arch, kAnyShape, &any, nullptr);
+    if (!rc) rc = conv2d_config_check(s, &any, dev.lds_limit);
+    if (!rc) *c = any;
+    return rc;
+}
+
 int cache_store(const std::string& path, const std::string& arch, const conv2d_shape& s,
                 const conv2d_config& c, double ms)
 {
