@@ -82,6 +82,9 @@ static void batch_free(conv2d_batch_s* b)
     delete b;
 }
 
+// Size of a table of tile owners: the kernel reads it by whole dwords.
+static size_t owner_bytes(size_t n) { return (sizeof(unsigned short) * n + 3) / 4 * 4; }
+
 static int launch_group(const Group& g, hipStream_t st)
 {
     return launch_batch_kernel(g.mod, g.cfg, g.grid, g.a_desc, g.a_owner, g.a_total, st);
@@ -327,7 +330,7 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     // Device tables: descriptors (pointers filled at run time) and tile owners.
     if (hipHostMalloc((void**)&b->h_desc, sizeof(ConvDesc) * n, hipHostMallocDefault) != hipSuccess ||
         hipMalloc((void**)&b->d_desc, sizeof(ConvDesc) * n) != hipSuccess ||
-        hipMalloc((void**)&b->d_owner, sizeof(unsigned short) * owner.size()) != hipSuccess)
+        hipMalloc((void**)&b->d_owner, owner_bytes(owner.size())) != hipSuccess)
         return fail(CONV2D_ENOMEM, "batch: allocation of the descriptor tables failed");
     std::memcpy(b->h_desc, proto.data(), sizeof(ConvDesc) * n);
     CONV2D_HIP(hipMemcpy(b->d_owner, owner.data(), sizeof(unsigned short) * owner.size(), hipMemcpyHostToDevice));
@@ -580,7 +583,7 @@ struct GroupBench {
         tiles = (int)total;
         if (d_owner) hipFree(d_owner);
         d_owner = nullptr;
-        if (hipMalloc(&d_owner, sizeof(unsigned short) * owner.size()) != hipSuccess)
+        if (hipMalloc(&d_owner, owner_bytes(owner.size())) != hipSuccess)
             return fail(CONV2D_ENOMEM, "batch tune: device allocation");
         CONV2D_HIP(hipMemcpy(d_desc, descs.data(), sizeof(ConvDesc) * descs.size(), hipMemcpyHostToDevice));
         CONV2D_HIP(hipMemcpy(d_owner, owner.data(), sizeof(unsigned short) * owner.size(), hipMemcpyHostToDevice));

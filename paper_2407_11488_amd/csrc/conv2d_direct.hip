@@ -133,6 +133,18 @@ __constant__ float conv_filter[CONV_FH * CONV_FW];
 #define TAPS filt
 #endif
 
+// Pointers that come out of a descriptor could point anywhere as far as the
+// compiler knows; it reads and writes through them with flat accesses, the taps
+// by vector loads in every row. Constant memory for the taps gives scalar loads,
+// global memory for the outputs plain stores.
+#if CONV_BATCH && defined(__AMDGCN__)
+typedef const __attribute__((address_space(4))) float* TapPtr;
+#define CONV_GLOBAL __attribute__((address_space(1)))
+#else
+typedef const float* __restrict__ TapPtr;
+#define CONV_GLOBAL
+#endif
+
 static __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const float* p, u32 bytes)
 {
     // Word 3 = 0x00020000: raw (untyped) dword access, the gfx9-family value.
@@ -270,7 +282,7 @@ struct MatrixRows {
     // Block row p's first (MY = 0, filter row 0) or last input row (MY = 1,
     // filter row FH - 1): one output row of the two, plain FMAs.
     template <int MY>
-    __device__ __forceinline__ void rim(int p, const float* w, const float* __restrict__ ft)
+    __device__ __forceinline__ void rim(int p, const float* w, TapPtr ft)
     {
 #pragma unroll
         for (int j = 0; j < FW; ++j) {
@@ -285,7 +297,7 @@ struct MatrixRows {
 
     // Column k = 0 (FIRSTCOL) or FW of block row p at its input row i.
     template <bool FIRSTCOL>
-    __device__ __forceinline__ void side(int p, int i, const float* w, const float* __restrict__ ft)
+    __device__ __forceinline__ void side(int p, int i, const float* w, TapPtr ft)
     {
         constexpr int J = FIRSTCOL ? 0 : FW - 1, K = FIRSTCOL ? 0 : FW, X = FIRSTCOL ? 0 : 1;
         const float f0 = ft[i * FW + J], f1 = ft[(i - 1) * FW + J];
@@ -302,7 +314,7 @@ struct MatrixRows {
     // other and back costs about 6 cycles (14 cycles for one of each become
     // 21 when they alternate).
     template <bool STEADY, class Rsrc>
-    __device__ __forceinline__ void row(int r, const float* w, Rsrc rf, u32 lane_off, const float* __restrict__ ft)
+    __device__ __forceinline__ void row(int r, const float* w, Rsrc rf, u32 lane_off, TapPtr ft)
     {
         constexpr int kFence = 0x4 | 0x10 | 0x80;   // scalar and memory instructions may cross, ALU ones not
         float a[NP][NA];
@@ -344,17 +356,25 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
                                                  int tile_x, int tile_y, float* __restrict__ lds)
 {
     using G = Geo<FH, FW, BX, BY, TX, TY, LDS, UNROLL, VIN, VOUT>;
-    const int lx = (int)threadIdx.x % BX;
-    const int ly = (int)threadIdx.x / BX;
+    int tid = (int)threadIdx.x;
+#if CONV_BATCH && defined(__AMDGCN__)
+    // Keeps what depends on the thread inside the batched kernel's tile loop,
+    // which nearly always runs once: hoisted out, it held 26 registers at 17 x
+    // 17.
+    asm volatile("" : "+v"(tid));
+#endif
+    const int lx = tid % BX;
+    const int ly = tid / BX;
     const int x0 = tile_x * (BX * TX) + lx * TX;
     const int y0 = tile_y * (BY * TY) + ly * TY;
     const u32 P = (u32)W + (FW - 1);
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(in, in_bytes);
+    TapPtr const taps = (TapPtr)TAPS;
 
 #if CONV_HAVE_MFMA
     using M = MatrixRows<FH, FW, TX, TY, G>;
     M m;
-    const u32 lane = threadIdx.x & 63u;
+    const u32 lane = (u32)tid & 63u;
     const u32 lane_off = ((1u - ((lane >> 1) & 1u)) * FW + (lane >> 2) + 1u - (lane & 1u)) * 4u;
     const __amdgpu_buffer_rsrc_t rf = make_rsrc(filt, FH * FW * 4u);
     if constexpr (G::MATRIX && M::HOLD) {
@@ -373,7 +393,7 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
         constexpr int STEPS = (G::LDS_ROWS * G::LDS_CHUNKS + G::NT - 1) / G::NT;
         constexpr int STAGE = min_(STEPS, 8);
         constexpr int DR = G::NT / G::LDS_CHUNKS, DC = G::NT % G::LDS_CHUNKS;
-        int c = (int)threadIdx.x;
+        int c = tid;
         int cc = c % G::LDS_CHUNKS, rr = c / G::LDS_CHUNKS;
         u32 off = (((u32)tile_y * (BY * TY) + (u32)rr) * P + (u32)tile_x * (BX * TX) + (u32)(cc * VIN)) * 4u;
         float* dst = lds + rr * G::LDS_PITCH + cc * VIN;
@@ -443,26 +463,26 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
             for (int r = 0; r < M::FIRST; ++r) {
                 float w[G::WIN_PAD];
                 window(w, r);
-                m.template row<false>(r, w, rf, lane_off, TAPS);
+                m.template row<false>(r, w, rf, lane_off, taps);
             }
 #pragma unroll G::ROW_UNROLL
             for (int r = M::FIRST; r <= M::LAST; ++r) {
                 float w[G::WIN_PAD];
                 window(w, r);
-                m.template row<true>(r, w, rf, lane_off, TAPS);
+                m.template row<true>(r, w, rf, lane_off, taps);
             }
 #pragma unroll
             for (int r = M::LAST + 1; r < G::NROWS; ++r) {
                 float w[G::WIN_PAD];
                 window(w, r);
-                m.template row<false>(r, w, rf, lane_off, TAPS);
+                m.template row<false>(r, w, rf, lane_off, taps);
             }
         } else {
 #pragma unroll
             for (int r = 0; r < G::NROWS; ++r) {
                 float w[G::WIN_PAD];
                 window(w, r);
-                m.template row<false>(r, w, rf, lane_off, TAPS);
+                m.template row<false>(r, w, rf, lane_off, taps);
             }
         }
 #pragma unroll
@@ -497,7 +517,7 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
             if (i >= 0 && i < FH) {
 #pragma unroll
                 for (int j = 0; j < FW; ++j) {
-                    const float fv = TAPS[i * FW + j];
+                    const float fv = taps[i * FW + j];
 #pragma unroll
                     for (int k = 0; k < TX; ++k)
                         acc[o][k] = __builtin_fmaf(w[k + j], fv, acc[o][k]);
@@ -511,16 +531,16 @@ static __device__ __forceinline__ void conv_tile(const float* __restrict__ in, c
     for (int o = 0; o < TY; ++o) {
         const int y = y0 + o;
         if (y < H) {
-            float* orow = out + (size_t)y * (size_t)W + x0;
+            CONV_GLOBAL float* orow = (CONV_GLOBAL float*)out + (size_t)y * (size_t)W + x0;
             if (x0 + TX <= W) {
 #pragma unroll
                 for (int k = 0; k < TX; k += G::SVEC) {
                     if constexpr (G::SVEC == 4) {
                         f32x4 v = {acc[o][k], acc[o][k + 1], acc[o][k + 2], acc[o][k + 3]};
-                        __builtin_nontemporal_store(v, (f32x4*)(orow + k));
+                        __builtin_nontemporal_store(v, (CONV_GLOBAL f32x4*)(orow + k));
                     } else if constexpr (G::SVEC == 2) {
                         f32x2 v = {acc[o][k], acc[o][k + 1]};
-                        __builtin_nontemporal_store(v, (f32x2*)(orow + k));
+                        __builtin_nontemporal_store(v, (CONV_GLOBAL f32x2*)(orow + k));
                     } else {
                         __builtin_nontemporal_store(acc[o][k], orow + k);
                     }
@@ -565,13 +585,33 @@ struct ConvDesc {
     int n_tiles;      // tiles of this problem
 };
 
-// The descriptor of tile t. The owner is read with a 16-bit vector load (no
-// 16-bit scalar load on gfx9); it is the same for every lane, and saying so
-// keeps the descriptor, the filter taps and all addressing in scalar registers.
-static __device__ __forceinline__ const ConvDesc* tile_desc(const ConvDesc* __restrict__ descs,
-                                                            const unsigned short* __restrict__ owner, int t)
+// The descriptor of tile t, in scalar registers (it is the same for every
+// lane, and all addressing and the filter taps follow from it). There is no
+// 16-bit scalar load on gfx9: the aligned dword that holds the tile's owner is
+// read (the library allocates its tables in whole dwords). The descriptor comes
+// in one go, so what a workgroup waits for before its first input load is
+// arguments, owner, descriptor, one after another. With a vector load for the
+// owner, the descriptor field by field, and its pointers read through as if
+// they could point anywhere (see TapPtr), one image of 4096 x 4096 took 5 x 5
+// 23.9 us (now 21.3), 9 x 9 43.1 (41.1) and 3 x 3 21.4 (20.0), and 64 images up
+// to 2048 took 225 us (214).
+static __device__ __forceinline__ ConvDesc tile_desc(const ConvDesc* __restrict__ descs,
+                                                     const unsigned short* __restrict__ owner, int t)
 {
-    return descs + __builtin_amdgcn_readfirstlane((int)owner[t]);
+#if defined(__AMDGCN__)
+    typedef const __attribute__((address_space(4))) u32 cu32;
+    typedef const __attribute__((address_space(4))) u32x4 cu32x4;
+    struct Words {
+        u32x4 a, b, c;
+    };
+    const unsigned long long at = (unsigned long long)(owner + t);
+    const u32 who = (*(cu32*)(at & ~3ull) >> ((u32)(at & 2u) * 8u)) & 0xffffu;
+    cu32x4* from = (cu32x4*)(unsigned long long)(descs + who);
+    const Words w = {from[0], from[1], from[2]};
+    return __builtin_bit_cast(ConvDesc, w);
+#else
+    return descs[owner[t]];
+#endif
 }
 
 // Many images with the same filter size: a grid of at least 8 workgroups
@@ -585,6 +625,9 @@ CONV_NAME(const ConvDesc* __restrict__ descs, const unsigned short* __restrict__
 {
     __shared__ __attribute__((aligned(16))) float lds[G1::LDS_FLOATS];
     const int G = (int)gridDim.x;
+#if defined(__AMDGCN__)
+    asm volatile("" : : "s"(descs), "s"(owner), "s"(total_tiles), "s"(G));
+#endif
     const int xcd = (int)blockIdx.x & 7;
     const int first = (int)blockIdx.x >> 3;
     const int stride = (G - xcd + 7) >> 3;
@@ -593,16 +636,16 @@ CONV_NAME(const ConvDesc* __restrict__ descs, const unsigned short* __restrict__
     const int count = q + (xcd < rem ? 1 : 0);
     for (int k = first; k < count; k += stride) {
         const int t = begin + k;
-        const ConvDesc* d = tile_desc(descs, owner, t);
-        const int lt = t - d->tile_begin;
-        if ((unsigned)lt >= (unsigned)d->n_tiles)
+        const ConvDesc d = tile_desc(descs, owner, t);
+        const int lt = t - d.tile_begin;
+        if ((unsigned)lt >= (unsigned)d.n_tiles)
             continue;  // inconsistent tables: skip rather than store out of range (uniform)
-        const int tile_y = lt / d->tiles_x;
-        const int tile_x = lt - tile_y * d->tiles_x;
+        const int tile_y = lt / d.tiles_x;
+        const int tile_x = lt - tile_y * d.tiles_x;
         if (CONV_USE_LDS && k != first)
             __syncthreads();  // every thread is done with the previous tile's LDS
         conv_tile<CONV_FH, CONV_FW, CONV_BX, CONV_BY, CONV_TX, CONV_TY, CONV_USE_LDS, CONV_UNROLL, CONV_VIN, CONV_VOUT>(
-            d->in, d->filt, d->out, d->H, d->W, d->in_bytes, tile_x, tile_y, lds);
+            d.in, d.filt, d.out, d.H, d.W, d.in_bytes, tile_x, tile_y, lds);
     }
 }
 #endif
