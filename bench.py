@@ -23,8 +23,8 @@ import time
 
 H = W = 4096
 FH = FW = 17
-PEAK_FP32_TFLOPS = 157.3          # MI355X published FP32 vector peak (packed FP32)
-PEAK_FP32_UNPACKED_TFLOPS = 78.6  # 256 CU x 64 lanes x 2 FLOP x 2.4 GHz, one FMA per lane per clock
+PEAK_FP32_TFLOPS = 157.3          # MI355X published FP32 peak (matrix, or vector with packed FP32)
+PEAK_FP32_UNPACKED_TFLOPS = 78.6  # vector only: 256 CU x 64 lanes x 2 FLOP x 2.4 GHz, one FMA per lane per clock
 PEAK_HBM_GBS = 8000.0
 
 

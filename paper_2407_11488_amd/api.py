@@ -123,7 +123,8 @@ def reference(inp, filt, out=None, stream=None):
 
 
 class Batch:
-    """Many convolutions (uneven sizes, mixed filter sizes) run by one graph launch."""
+    """Many convolutions (uneven sizes, mixed filter sizes) run by one graph
+    launch, or as a few kernels where they are too small to pay for one."""
 
     def __init__(self, shapes, flags=0):
         self.shapes = [tuple(int(v) for v in s) for s in shapes]

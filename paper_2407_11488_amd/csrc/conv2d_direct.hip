@@ -626,6 +626,7 @@ CONV_NAME(const ConvDesc* __restrict__ descs, const unsigned short* __restrict__
     __shared__ __attribute__((aligned(16))) float lds[G1::LDS_FLOATS];
     const int G = (int)gridDim.x;
 #if defined(__AMDGCN__)
+    // The arguments are fetched together, not each where it is first used.
     asm volatile("" : : "s"(descs), "s"(owner), "s"(total_tiles), "s"(G));
 #endif
     const int xcd = (int)blockIdx.x & 7;
