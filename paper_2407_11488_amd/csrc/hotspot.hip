@@ -117,12 +117,28 @@ static __device__ __forceinline__ float lane_above(float x)
 // A cell's source term: its power and the ambient's share, per step.
 static __device__ __forceinline__ float source(float p, float cc, float q) { return __builtin_fmaf(cc, p, q); }
 
-static __device__ __forceinline__ float cell_step(float t, float north, float south, float west, float east, float src,
-                                                  float ka, float ky, float kx)
+// A cell's step in two parts: all but its own value, and that.
+static __device__ __forceinline__ float cell_sum(float north, float south, float west, float east, float src, float ky,
+                                                 float kx)
 {
-    float x = __builtin_fmaf(kx, west + east, src);
-    x = __builtin_fmaf(ky, north + south, x);
-    return __builtin_fmaf(ka, t, x);
+    return __builtin_fmaf(ky, north + south, __builtin_fmaf(kx, west + east, src));
+}
+// Tiles of up to 8 cells take the second part in place, after all sums. Left to
+// the compiler, the FMA writes the sum's register, and a step copies its cells:
+// 8 of the 52 vector instructions of a step of 8 cells. 60 steps at 4096 x 4096
+// took (32,16,2,4,8) 363.6 us (now 353.0), at 2048 x 2048 130.1 (127.5), 20
+// steps at 1000 x 1501 28.0 (27.6). Larger tiles would keep too many sums: 60
+// steps of 4 x 4 cells took 408 us that way and take 377 as the compiler orders
+// them.
+#define HS_IN_PLACE (HS_TX * HS_TY <= 8)
+static __device__ __forceinline__ float cell_add(float t, float ka, float sum)
+{
+#if HS_IN_PLACE && defined(__AMDGCN__)
+    asm("v_fma_f32 %0, %1, %0, %2" : "+v"(t) : "s"(ka), "v"(sum));
+    return t;
+#else
+    return __builtin_fmaf(ka, t, sum);
+#endif
 }
 
 // The launch's steps over the thread's cells v (in place). EDGE = false when
@@ -159,7 +175,7 @@ static __device__ __forceinline__ void run_steps(float (&v)[HS_TY][HS_TX], const
 #endif
         __syncthreads();
 
-        float nv[HS_TY][HS_TX];
+        float nv[HS_TY][HS_TX];   // the cells after the step, or their sums
 #pragma unroll
         for (int a = 0; a < HS_TY; ++a) {
             const int R = R0 + a, gr = gr0 + a;
@@ -211,14 +227,26 @@ static __device__ __forceinline__ void run_steps(float (&v)[HS_TY][HS_TX], const
                 const float src =
                     source(power[(size_t)clampi(gr, 0, rows - 1) * (size_t)cols + clampi(gc, 0, cols - 1)], cc, q);
 #endif
-                nv[a][b] = cell_step(t, north, south, west, east, src, ka, ky, kx);
+                nv[a][b] = cell_sum(north, south, west, east, src, ky, kx);
+                if (!HS_IN_PLACE)
+                    nv[a][b] = cell_add(t, ka, nv[a][b]);
             }
         }
 #pragma unroll
         for (int a = 0; a < HS_TY; ++a)
 #pragma unroll
             for (int b = 0; b < HS_TX; ++b)
-                v[a][b] = nv[a][b];
+                v[a][b] = HS_IN_PLACE ? cell_add(v[a][b], ka, nv[a][b]) : nv[a][b];
+#if HS_IN_PLACE && HS_ROWX && defined(__AMDGCN__)
+        // Two wait states between a vector write and a lane shift's read of it:
+        // the compiler does not see the writes inside cell_add().
+#pragma unroll
+        for (int a = 0; a < HS_TY; ++a) {
+            asm("s_nop 1" : "+v"(v[a][0]));
+            if (HS_TX > 1)
+                asm("s_nop 1" : "+v"(v[a][HS_TX - 1]));
+        }
+#endif
     }
 }
 
