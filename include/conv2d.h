@@ -235,7 +235,12 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * another. Results are bitwise identical to conv2d_run / conv2d_reference on
  * the same data.
  * A batch plan must not run on two streams at once (its descriptor table is
- * shared); runs on one stream are ordered. Each input is limited to 2 GiB. */
+ * shared); runs on one stream are ordered. A run on a stream under capture
+ * records its kernels with a descriptor table of their own: a replay works on
+ * the buffers of the recorded call, whatever the plan has run on since, and
+ * may overlap its other runs. Such tables are kept until the plan is
+ * destroyed, one for each set of buffers recorded. Each input is limited to
+ * 2 GiB. */
 
 enum {
     CONV2D_BATCH_NO_GRAPH = 1,     /* launch the group kernels directly instead of a graph */

@@ -36,8 +36,7 @@ struct Group {
     int threads = 0;
     size_t desc_begin = 0;       // first descriptor of the group
     size_t owner_begin = 0;      // first owner entry of the group
-    // kernel arguments, kept alive for graph capture and direct launches
-    const void* a_desc = nullptr;
+    // kernel arguments (beside the descriptor table)
     const void* a_owner = nullptr;
     int a_total = 0;
 };
@@ -63,6 +62,9 @@ struct conv2d_batch_s {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool direct = false;                 // small batch: see launch_directly
+    // Descriptor tables of runs recorded into a captured stream, by their
+    // pointers (see record()).
+    std::map<std::vector<const void*>, ConvDesc*> recorded;
     std::mutex mu;
 };
 
@@ -76,6 +78,7 @@ static void batch_free(conv2d_batch_s* b)
         hipEventDestroy(b->copied);
     }
     for (auto& g : b->groups) unload_module(&g.mod);
+    for (auto& kv : b->recorded) hipFree(kv.second);
     if (b->h_desc) hipHostFree(b->h_desc);
     if (b->d_desc) hipFree(b->d_desc);
     if (b->d_owner) hipFree(b->d_owner);
@@ -85,9 +88,10 @@ static void batch_free(conv2d_batch_s* b)
 // Size of a table of tile owners: the kernel reads it by whole dwords.
 static size_t owner_bytes(size_t n) { return (sizeof(unsigned short) * n + 3) / 4 * 4; }
 
-static int launch_group(const Group& g, hipStream_t st)
+// Launches a group on descriptor table `desc` (the whole batch's).
+static int launch_group(const Group& g, const ConvDesc* desc, hipStream_t st)
 {
-    return launch_batch_kernel(g.mod, g.cfg, g.grid, g.a_desc, g.a_owner, g.a_total, st);
+    return launch_batch_kernel(g.mod, g.cfg, g.grid, desc + g.desc_begin, g.a_owner, g.a_total, st);
 }
 
 // Does this batch run faster as plain launches than as its graph? Launching
@@ -136,7 +140,7 @@ static int capture(conv2d_batch_s* b)
             rc = hip_fail(e, "hipStreamWaitEvent (capture fork)");
             break;
         }
-        rc = launch_group(b->groups[g], st);
+        rc = launch_group(b->groups[g], b->d_desc, st);
         // The branch is joined back to the root stream even after a failed
         // launch, so that the capture can end.
         if ((e = hipEventRecord(events[g + 1], st)) != hipSuccess ||
@@ -336,7 +340,6 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     CONV2D_HIP(hipMemcpy(b->d_owner, owner.data(), sizeof(unsigned short) * owner.size(), hipMemcpyHostToDevice));
     CONV2D_HIP(hipEventCreateWithFlags(&b->copied, hipEventDisableTiming));
     for (auto& g : b->groups) {
-        g.a_desc = b->d_desc + g.desc_begin;
         g.a_owner = b->d_owner + g.owner_begin;
         g.a_total = g.total_tiles;
     }
@@ -346,6 +349,88 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
         b->direct = launch_directly(b.get());
     }
     *out = b.release();
+    return CONV2D_OK;
+}
+
+// Checks the pointers of a run (in, filter and out of each problem, in order).
+static int check_problems(const conv2d_batch_s* b, const std::vector<const void*>& ptrs)
+{
+    if (b->flags & CONV2D_BATCH_NO_PTR_CHECK) return CONV2D_OK;
+    for (size_t i = 0; i < b->shapes.size(); ++i) {
+        const conv2d_shape& s = b->shapes[i];
+        const size_t in_b = 4ull * ((size_t)s.out_h + s.filt_h - 1) * ((size_t)s.out_w + s.filt_w - 1);
+        const size_t f_b = 4ull * s.filt_h * s.filt_w, o_b = 4ull * s.out_h * s.out_w;
+        int rc = check_device_range(ptrs[3 * i], in_b, "d_in");
+        if (!rc) rc = check_device_range(ptrs[3 * i + 1], f_b, "d_filter");
+        if (!rc) rc = check_device_range(ptrs[3 * i + 2], o_b, "d_out");
+        if (rc) return fail(rc, "problem " + std::to_string(i) + ": " + last_error_cstr());
+        const uintptr_t a = (uintptr_t)ptrs[3 * i], f = (uintptr_t)ptrs[3 * i + 1], o = (uintptr_t)ptrs[3 * i + 2];
+        if ((o < a + in_b && a < o + o_b) || (o < f + f_b && f < o + o_b))
+            return fail(CONV2D_EINVAL, "problem " + std::to_string(i) + ": d_out overlaps its inputs");
+    }
+    return CONV2D_OK;
+}
+
+// Writes the pointers of a run into the descriptors.
+static void set_pointers(const conv2d_batch_s* b, const std::vector<const void*>& ptrs, ConvDesc* desc)
+{
+    for (size_t i = 0; i < b->shapes.size(); ++i) {
+        ConvDesc& d = desc[b->desc_slot[i]];
+        d.in = static_cast<const float*>(ptrs[3 * i]);
+        d.filt = static_cast<const float*>(ptrs[3 * i + 1]);
+        d.out = static_cast<float*>(const_cast<void*>(ptrs[3 * i + 2]));
+    }
+}
+
+// Allocates a descriptor table on the device and fills it at once, beside any
+// capture in progress (the calling thread is in the relaxed capture mode).
+static hipError_t new_table(const std::vector<ConvDesc>& desc, ConvDesc** out)
+{
+    const size_t bytes = sizeof(ConvDesc) * desc.size();
+    hipStream_t st = nullptr;
+    ConvDesc* d = nullptr;
+    hipError_t e = hipMalloc((void**)&d, bytes);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipMemcpyAsync(d, desc.data(), bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (st) hipStreamDestroy(st);
+    if (e == hipSuccess) *out = d;
+    else if (d) hipFree(d);
+    return e;
+}
+
+// A run on a stream under capture records its kernels (a graph launched into
+// it would run at once and record nothing). The plan's own table belongs to
+// the runs that are not recorded, which rewrite it, and a recorded upload would
+// not have happened yet when the next such run relies on it. So the recorded
+// kernels read a table of their own, which is complete when this returns and
+// never changes: a replay works on the buffers of the recorded call, whatever
+// ran in between, and nothing that the other runs go by is touched. Recordings
+// on the same buffers share a table; all are freed with the plan.
+static int record(conv2d_batch_s* b, const std::vector<const void*>& ptrs, hipStream_t st)
+{
+    int rc = check_problems(b, ptrs);
+    if (rc) return rc;
+    auto it = b->recorded.find(ptrs);
+    if (it == b->recorded.end()) {
+        std::vector<ConvDesc> desc(b->h_desc, b->h_desc + b->shapes.size());
+        set_pointers(b, ptrs, desc.data());
+        ConvDesc* d = nullptr;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        CONV2D_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+        const hipError_t e = new_table(desc, &d);
+        CONV2D_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e == hipErrorOutOfMemory ? fail(CONV2D_ENOMEM, "batch: allocation of a recorded run's table failed")
+                                            : hip_fail(e, "batch: table of a recorded run");
+        }
+        it = b->recorded.emplace(ptrs, d).first;
+    }
+    for (const auto& g : b->groups) {
+        rc = launch_group(g, it->second, st);
+        if (rc) return rc;
+    }
     return CONV2D_OK;
 }
 
@@ -367,48 +452,32 @@ extern "C" int conv2d_batch_run(conv2d_batch_t b, const float* const* d_in, cons
         ptrs[3 * i + 1] = d_f[i];
         ptrs[3 * i + 2] = d_out[i];
     }
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &capturing) != hipSuccess) {   // the null stream cannot be captured
+        (void)hipGetLastError();
+        capturing = hipStreamCaptureStatusNone;   // the calls below report what is wrong with the stream
+    }
+    if (capturing != hipStreamCaptureStatusNone) return record(b, ptrs, st);
+
     if (ptrs != b->uploaded) {
-        if (!(b->flags & CONV2D_BATCH_NO_PTR_CHECK)) {
-            for (int i = 0; i < n; ++i) {
-                const conv2d_shape& s = b->shapes[i];
-                const size_t in_b = 4ull * ((size_t)s.out_h + s.filt_h - 1) * ((size_t)s.out_w + s.filt_w - 1);
-                const size_t f_b = 4ull * s.filt_h * s.filt_w, o_b = 4ull * s.out_h * s.out_w;
-                int rc = check_device_range(d_in[i], in_b, "d_in");
-                if (!rc) rc = check_device_range(d_f[i], f_b, "d_filter");
-                if (!rc) rc = check_device_range(d_out[i], o_b, "d_out");
-                if (rc) return fail(rc, "problem " + std::to_string(i) + ": " + last_error_cstr());
-                const uintptr_t o = (uintptr_t)d_out[i], a = (uintptr_t)d_in[i], f = (uintptr_t)d_f[i];
-                if ((o < a + in_b && a < o + o_b) || (o < f + f_b && f < o + o_b))
-                    return fail(CONV2D_EINVAL, "problem " + std::to_string(i) + ": d_out overlaps its inputs");
-            }
-        }
+        int rc = check_problems(b, ptrs);
+        if (rc) return rc;
         // The staging buffer may still feed the previous upload.
         if (b->copy_pending) CONV2D_HIP(hipEventSynchronize(b->copied));
-        for (int i = 0; i < n; ++i) {
-            ConvDesc& d = b->h_desc[b->desc_slot[i]];
-            d.in = d_in[i];
-            d.filt = d_f[i];
-            d.out = d_out[i];
-        }
+        set_pointers(b, ptrs, b->h_desc);
+        b->uploaded.clear();
         CONV2D_HIP(hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(ConvDesc) * n, hipMemcpyHostToDevice, st));
         CONV2D_HIP(hipEventRecord(b->copied, st));
         b->copy_pending = true;
         b->uploaded = ptrs;
     }
-    // A stream that is being captured records the kernels themselves (a graph
-    // launched into it runs at once and leaves the captured graph empty).
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (b->exec && !b->direct && hipStreamIsCapturing(st, &capturing) != hipSuccess) {
-        (void)hipGetLastError();
-        capturing = hipStreamCaptureStatusActive;
-    }
-    if (b->exec && !b->direct && capturing == hipStreamCaptureStatusNone) {
+    if (b->exec && !b->direct) {
         hipError_t e = hipGraphLaunch(b->exec, st);
         if (e != hipSuccess) return fail(CONV2D_ELAUNCH, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
         return CONV2D_OK;
     }
     for (const auto& g : b->groups) {
-        int rc = launch_group(g, st);
+        int rc = launch_group(g, b->d_desc, st);
         if (rc) return rc;
     }
     return CONV2D_OK;
