@@ -232,7 +232,7 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * runs). The
  * groups are parallel branches of one graph captured at plan time; a batch too
  * small to pay for the graph's launch has its kernels launched one after
- * another. Results are bitwise identical to conv2d_run / conv2d_reference on
+ * another (conv2d_batch_uses_graph tells). Results are bitwise identical to conv2d_run / conv2d_reference on
  * the same data.
  * A batch plan must not run on two streams at once (its descriptor table is
  * shared); runs on one stream are ordered. A run on a stream under capture
@@ -269,6 +269,11 @@ int conv2d_batch_run(conv2d_batch_t batch, const float *const *d_in, const float
  * Source: Table 1 (the configuration of each group). */
 int conv2d_batch_info(conv2d_batch_t batch, int *n_groups, int *total_tiles, int *filt,
                       conv2d_config *cfgs, int *grids, int cap);
+
+/* *graph = 1 when a run of the batch is one graph launch, 0 when its kernels
+ * are launched one after another (a small batch, or CONV2D_BATCH_NO_GRAPH).
+ * Source: none in the paper (how this library launches a batch). */
+int conv2d_batch_uses_graph(conv2d_batch_t batch, int *graph);
 
 /* Frees the batch: its code objects and device buffers. It does not wait:
  * the caller first makes sure that no launch of the batch is queued or

@@ -279,6 +279,7 @@ for _name, (_res, _args) in {
     "conv2d_batch_plan": (c_int, [P(c_void_p), c_int, P(Shape), c_int]),
     "conv2d_batch_run": (c_int, [c_void_p, P(c_void_p), P(c_void_p), P(c_void_p), c_void_p]),
     "conv2d_batch_info": (c_int, [c_void_p, P(c_int), P(c_int), P(c_int), P(Config), P(c_int), c_int]),
+    "conv2d_batch_uses_graph": (c_int, [c_void_p, P(c_int)]),
     "conv2d_batch_destroy": (None, [c_void_p]),
     "conv2d_compile_batch": (c_int, [Shape, P(Config), c_char_p, c_int]),
     "conv2d_warm_cache": (c_int, [c_char_p, c_int, P(c_int), P(c_int)]),
@@ -311,7 +312,14 @@ def conv2d_batch_info(batch: int, cap: int = 64) -> dict:
           "conv2d_batch_info")
     groups = [{"filter": (filt[2 * g], filt[2 * g + 1]), "config": cfgs[g].tuple(), "grid": grids[g]}
               for g in range(min(ng.value, cap))]
-    return {"n_groups": ng.value, "total_tiles": tiles.value, "groups": groups}
+    return {"n_groups": ng.value, "total_tiles": tiles.value, "groups": groups,
+            "graph": conv2d_batch_uses_graph(batch)}
+
+
+def conv2d_batch_uses_graph(batch: int) -> bool:
+    graph = c_int()
+    check(lib.conv2d_batch_uses_graph(batch, ctypes.byref(graph)), "conv2d_batch_uses_graph")
+    return bool(graph.value)
 
 
 BATCH_TUNE_MAX = 32

@@ -60,8 +60,7 @@ struct conv2d_batch_s {
     hipEvent_t copied = nullptr;
     bool copy_pending = false;
     hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    bool direct = false;                 // small batch: see launch_directly
+    hipGraphExec_t exec = nullptr;       // none: launch_directly, or CONV2D_BATCH_NO_GRAPH
     // Descriptor tables of runs recorded into a captured stream, by their
     // pointers (see record()).
     std::map<std::vector<const void*>, ConvDesc*> recorded;
@@ -98,11 +97,14 @@ static int launch_group(const Group& g, const ConvDesc* desc, hipStream_t st)
 // the graph costs the host about 13 us per branch (10-14 us measured for 2 to
 // 6 branches), a plain launch 3 to 4 us, and the GPU gets the work that much
 // later; against that, parallel branches fill the tails of each other's
-// kernels. Measured per run, graph and direct: 16 images up to 768 (6 kernels)
-// 81 and 36 us, 4 images up to 512 (2 kernels) 38 and 14 us, 40 images up to
-// 1024 (6 kernels) 81 and 54 us; 64 images up to 2048 (4 kernels, 13.4 GFLOP)
-// 211 and 215 us. The line is where the kernels take 25 us per branch, at the
-// 65 TFLOP/s the large batch reaches.
+// kernels. The line is where the kernels take 25 us per branch at 65 TFLOP/s,
+// between the 52 that 64 images up to 1024 reach and the 85 of 64 up to 2048.
+// Measured per run, graph and direct, and what the rule estimates a branch:
+// 16 images up to 2048 (4 kernels, 3.5 us) 85 and 32 us, 64 up to 1024 (4,
+// 10.9 us) 88 and 54, 32 up to 2048 by size (5, 24.5 us) 110 and 106, 64 up to
+// 2048 (4, 73 us) 223 and 224, by size (7, 42 us) 244 and 248. Small filters,
+// bound by bytes, take longer than estimated and still run no slower directly:
+// 64 images up to 2048 under 3 x 3 and 5 x 5 148 and 134 us.
 static bool launch_directly(const conv2d_batch_s* b)
 {
     double flops = 0;
@@ -343,10 +345,9 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
         g.a_owner = b->d_owner + g.owner_begin;
         g.a_total = g.total_tiles;
     }
-    if (!(flags & CONV2D_BATCH_NO_GRAPH)) {
+    if (!(flags & CONV2D_BATCH_NO_GRAPH) && !launch_directly(b.get())) {
         rc = capture(b.get());
         if (rc) return rc;
-        b->direct = launch_directly(b.get());
     }
     *out = b.release();
     return CONV2D_OK;
@@ -471,7 +472,7 @@ extern "C" int conv2d_batch_run(conv2d_batch_t b, const float* const* d_in, cons
         b->copy_pending = true;
         b->uploaded = ptrs;
     }
-    if (b->exec && !b->direct) {
+    if (b->exec) {
         hipError_t e = hipGraphLaunch(b->exec, st);
         if (e != hipSuccess) return fail(CONV2D_ELAUNCH, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
         return CONV2D_OK;
@@ -499,6 +500,14 @@ extern "C" int conv2d_batch_info(conv2d_batch_t b, int* n_groups, int* total_til
     }
     if (n_groups) *n_groups = (int)b->groups.size();
     if (total_tiles) *total_tiles = tiles;
+    return CONV2D_OK;
+}
+
+extern "C" int conv2d_batch_uses_graph(conv2d_batch_t b, int* graph)
+{
+    clear_error();
+    if (!b || !graph) return fail(CONV2D_EINVAL, "batch and graph must be non-NULL");
+    *graph = b->exec ? 1 : 0;
     return CONV2D_OK;
 }
 
