@@ -168,9 +168,10 @@ int conv2d_cache_store(const char *path, const char *arch, conv2d_shape s,
  * the same filter size for another shape (4096 x 4096 first, else the most
  * recent) when it is legal for this shape, else the cache's entry for any
  * shape, (-1, -1, 0, 0), else the default configuration (below 2^22 outputs
- * the entry for any shape comes before the filter's); the environment
- * variable CONV2D_FORCE_CONFIG ("bx,by,tx,ty,lds,const,unroll") overrides
- * them all. Compiles (or loads from the code-object cache) and loads the module. The plan owns the module.
+ * the entry for any shape comes before a winner of the filter that was tuned at
+ * 2^22 outputs or more); the environment variable CONV2D_FORCE_CONFIG
+ * ("bx,by,tx,ty,lds,const,unroll") overrides them all. Compiles (or loads from
+ * the code-object cache) and loads the module. The plan owns the module.
  * Source: Section 5 (the convolution benchmark kernel) with a point of the
  * Table 1 space; the formula is the one at the top of this header. */
 int conv2d_plan(conv2d_plan_t *plan, conv2d_shape s, const conv2d_config *cfg);
@@ -224,8 +225,9 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * whole-batch entry (0, 0, fh, fw) from conv2d_batch_tune, else its size
  * bucket's entry (0, b, fh, fw) (with CONV2D_BATCH_BY_SIZE the other way
  * round), else the winners cache entry for 4096x4096 with that filter, else
- * the most recent entry with that filter, else the entry for any shape (before
- * the filter's with CONV2D_BATCH_BY_SIZE up to 1536), else the default; the
+ * the most recent entry with that filter, else the entry for any shape (with
+ * CONV2D_BATCH_BY_SIZE, up to 1536, before a winner of the filter tuned at 2^22
+ * outputs or more), else the default; the
  * filter is always read through its pointer. The problems sharing a filter size and
  * configuration form a group, run as one kernel over the group's tiles (a
  * workgroup per tile, the tiles of each image in row order, XCD-contiguous

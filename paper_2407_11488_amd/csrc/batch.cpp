@@ -190,9 +190,10 @@ int size_bucket(int out_h, int out_w)
 // The configuration the batched path uses for a filter size: with a size
 // bucket (> 0), the bucket's entry, else the filter's whole-batch entry;
 // without (bucket 0), the whole-batch entry, else the entry of the bucket
-// `fallback_bucket`; then the 4096x4096 winner (small buckets: the entry for
-// any shape first), else the entry for any shape, else the default. The filter
-// is read through its pointer.
+// `fallback_bucket`; then the 4096x4096 winner or the filter's most recent
+// entry (small buckets: the entry for any shape before a winner at 2^22 outputs
+// or more), else the entry for any shape, else the default. The filter is read
+// through its pointer.
 static conv2d_config lookup_batch_config(const DeviceInfo& dev, const std::string& wp, int fh, int fw, int bucket,
                                          int fallback_bucket = 0)
 {
@@ -201,8 +202,17 @@ static conv2d_config lookup_batch_config(const DeviceInfo& dev, const std::strin
     auto entry = [&](int b) { return cache_lookup(wp, dev.arch, batch_key(fh, fw, b), &cfg, nullptr) == CONV2D_OK; };
     bool found = bucket > 0 ? entry(bucket) || entry(0) : entry(0) || (fallback_bucket > 0 && entry(fallback_bucket));
     const bool small = bucket > 0 && bucket <= 3;   // sides up to 1536: below kSmallOutputs
-    if (!found && small) found = cache_lookup_any(wp, dev, tuned_shape, &cfg) == CONV2D_OK;
-    if (!found) found = cache_lookup_filter(wp, dev.arch, fh, fw, tuned_shape, &cfg) == CONV2D_OK;
+    if (!found) {
+        conv2d_config near{};   // the same filter's plain entry
+        conv2d_shape from{};
+        const bool have_near = cache_lookup_filter(wp, dev.arch, fh, fw, tuned_shape, &near, &from) == CONV2D_OK;
+        if (small && !(have_near && tuned_small(from)))
+            found = cache_lookup_any(wp, dev, tuned_shape, &cfg) == CONV2D_OK;
+        if (!found && have_near) {
+            cfg = near;
+            found = true;
+        }
+    }
     if (!found) found = cache_lookup_any(wp, dev, tuned_shape, &cfg) == CONV2D_OK;
     if (!found) conv2d_default_config(&cfg);
     clear_error();

@@ -209,9 +209,9 @@ int cache_lookup(const std::string& path, const std::string& arch, const conv2d_
 int cache_store(const std::string& path, const std::string& arch, const conv2d_shape& s,
                 const conv2d_config& c, double ms);
 // The winner for a filter size: the entry of `prefer` if cached, else the
-// most recent entry of any shape with that filter size.
+// most recent entry of any shape with that filter size. *from: its shape.
 int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
-                        const conv2d_shape& prefer, conv2d_config* c);
+                        const conv2d_shape& prefer, conv2d_config* c, conv2d_shape* from = nullptr);
 // The winners-cache shape of the configuration for any size and any filter: a
 // compromise over both, for shapes that have no better entry. It must be legal
 // for s.
@@ -224,6 +224,9 @@ int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2
 // 2.7 times as long up to 1400 x 1400 (31 x 31 on 512 x 512: 34.0 and 13.1 us,
 // 17 x 17 8.8 and 5.6), 0.97 to 1.08 at 2000 x 2000 and 0.93 to 1.0 at 2800 x
 // 2800.
+// An entry of the filter that was itself tuned on smaller sizes (tuned_small)
+// still comes first, as it does above that line.
 constexpr long long kSmallOutputs = 1ll << 22;
+bool tuned_small(const conv2d_shape& entry);
 
 }  // namespace conv2d

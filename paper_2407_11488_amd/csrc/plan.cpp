@@ -245,21 +245,29 @@ extern "C" int conv2d_plan(conv2d_plan_t* plan, conv2d_shape s, const conv2d_con
         std::string wp = env_str("CONV2D_WINNERS");
         if (wp.empty()) wp = winners_default_path();
         bool stale = false;
-        if (cache_lookup(wp, dev.arch, s, &p->cfg, &ms, &stale) == CONV2D_OK) {
+        conv2d_config own{}, near{}, any{};
+        conv2d_shape from{};
+        const bool have_own = cache_lookup(wp, dev.arch, s, &own, &ms, &stale) == CONV2D_OK;
+        // The same filter's winner for another shape (4096 x 4096 first).
+        const bool have_near = !have_own &&
+                               cache_lookup_filter(wp, dev.arch, s.filt_h, s.filt_w,
+                                                   conv2d_shape{4096, 4096, s.filt_h, s.filt_w}, &near,
+                                                   &from) == CONV2D_OK &&
+                               conv2d_config_check(s, &near, dev.lds_limit) == CONV2D_OK;
+        const bool have_any = !have_own && cache_lookup_any(wp, dev, s, &any) == CONV2D_OK;
+        const bool small = (long long)s.out_h * s.out_w < kSmallOutputs;
+        if (have_own) {
+            p->cfg = own;
             p->source = stale ? 3 : 1;
-        } else if ((long long)s.out_h * s.out_w < kSmallOutputs && cache_lookup_any(wp, dev, s, &p->cfg) == CONV2D_OK) {
+        } else if (have_near && !(have_any && small && !tuned_small(from))) {
+            p->cfg = near;
             p->source = 4;
-        } else if (cache_lookup_filter(wp, dev.arch, s.filt_h, s.filt_w, conv2d_shape{4096, 4096, s.filt_h, s.filt_w},
-                                       &p->cfg) == CONV2D_OK &&
-                   conv2d_config_check(s, &p->cfg, dev.lds_limit) == CONV2D_OK) {
-            // No entry for this shape: the same filter's winner for another
-            // shape (4096 x 4096 first) usually beats the default by far.
-            p->source = 4;
-        } else if (cache_lookup_any(wp, dev, s, &p->cfg) == CONV2D_OK) {
-            // A filter nobody tuned: against the default, the entry for any
-            // shape takes 0.42 of the time (geometric mean of 14 filters from
+        } else if (have_any) {
+            // Small, or a filter nobody tuned: against the default, the entry
+            // for any shape takes 0.42 of the time (geometric mean of 14 filters from
             // 1 x 1 to 45 x 17 at 128 x 128 to 3000 x 2500; at worst 0.74) and
             // stays within 2 % of the best of 14 candidates.
+            p->cfg = any;
             p->source = 4;
         } else {
             conv2d_default_config(&p->cfg);

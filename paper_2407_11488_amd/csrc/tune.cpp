@@ -78,14 +78,18 @@ int cache_lookup(const std::string& path, const std::string& arch, const conv2d_
 }
 
 int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
-                        const conv2d_shape& prefer, conv2d_config* c)
+                        const conv2d_shape& prefer, conv2d_config* c, conv2d_shape* from)
 {
-    if (cache_lookup(path, arch, prefer, c, nullptr) == CONV2D_OK) return CONV2D_OK;
+    if (cache_lookup(path, arch, prefer, c, nullptr) == CONV2D_OK) {
+        if (from) *from = prefer;
+        return CONV2D_OK;
+    }
     std::ifstream f(path);
     if (!f) return fail(CONV2D_ENOTUNED, "no winners cache at " + path);
     const std::string src = hex64(direct_source_hash());
     bool have_cur = false, have_old = false;
     conv2d_config cur{}, old{};
+    conv2d_shape cur_s{}, old_s{};
     std::string line;
     while (std::getline(f, line)) {
         JsonObj o;
@@ -93,14 +97,23 @@ int cache_lookup_filter(const std::string& path, const std::string& arch, int fh
         auto it = o.arr.find("shape");
         if (it == o.arr.end() || it->second.size() != 4 || (int)it->second[2] != fh || (int)it->second[3] != fw)
             continue;
+        const conv2d_shape ss{(int)it->second[0], (int)it->second[1], fh, fw};
         conv2d_config cc;
         if (!json_config(o, &cc)) continue;
-        if (o.str["src"] == src) { cur = cc; have_cur = true; }
-        else { old = cc; have_old = true; }
+        if (o.str["src"] == src) { cur = cc; cur_s = ss; have_cur = true; }
+        else { old = cc; old_s = ss; have_old = true; }
     }
     if (!have_cur && !have_old) return fail(CONV2D_ENOTUNED, "filter size not in winners cache");
     *c = have_cur ? cur : old;
+    if (from) *from = have_cur ? cur_s : old_s;
     return CONV2D_OK;
+}
+
+// Plain entries by their outputs, the batched path's (0, bucket, ..) by the
+// bucket: up to sides of 1536, or all sizes of a batch.
+bool tuned_small(const conv2d_shape& e)
+{
+    return e.out_h == 0 ? e.out_w <= 3 : (long long)e.out_h * e.out_w < kSmallOutputs;
 }
 
 int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2d_shape& s, conv2d_config* c)
