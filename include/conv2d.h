@@ -420,11 +420,13 @@ typedef struct conv2d_tune_opts {
     int retime_reps;           /* sustained launches re-timing the ten fastest (default 200) */
     int flush_mall;            /* 1: overwrite a 512 MiB buffer before each timed launch */
     int threads;               /* host compile threads (0: all cores, at most 16) */
-    int unroll;                /* unroll value for every point (default 1) */
+    int unroll;                /* unroll value for every point (default 1: every point on plain FMAs;
+                                  2 sweeps even tiles on the matrix cores) */
     int max_configs;           /* 0: whole space, else the first N legal points (tests) */
     double tie_rel;            /* relative tie window for the winner (default 0.005) */
     int verbose;               /* 1: progress lines on stderr */
-    int refine_unroll;         /* 1: also time the ten fastest points with the other unroll values */
+    int refine_unroll;         /* 1: also time the ten fastest points with the other unroll values (after
+                                  unroll 1 also the ten fastest that can use the matrix cores) */
     int strategy;              /* 0: brute force over the space (default); 1: random-restart hill
                                   climbing (one parameter one step per move; restart k starts at
                                   the idx-th unevaluated point in enumeration order,

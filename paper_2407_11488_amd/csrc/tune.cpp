@@ -595,6 +595,13 @@ int local_search(const conv2d_shape& s, const conv2d_tune_opts& o, Measurer* mea
     return CONV2D_OK;
 }
 
+// Does a point take the kernel's matrix path at an unroll other than 1?
+// (Geo::MATRIX in conv2d_direct.hip)
+bool matrix_with_unroll(const conv2d_shape& s, const conv2d_config& c)
+{
+    return c.tile_x % 2 == 0 && c.tile_y % 2 == 0 && c.block_x * c.block_y % 64 == 0 && s.filt_h >= 3 && s.filt_w >= 3;
+}
+
 int tune_core(const conv2d_shape& s, const conv2d_tune_opts& o, Measurer* meas, conv2d_tune_result* res)
 {
     *res = conv2d_tune_result{};
@@ -640,7 +647,10 @@ int tune_core(const conv2d_shape& s, const conv2d_tune_opts& o, Measurer* meas, 
     if (rc) return rc;
 
     // Optional refinement: the ten fastest points again with every other
-    // unroll value (the partial-unroll factor the paper makes tunable).
+    // unroll value (the partial-unroll factor the paper makes tunable). A sweep
+    // at unroll 1 times every point on plain FMAs, where odd tiles do as well
+    // as even ones; the ten fastest points that another unroll moves to the
+    // matrix cores come along, since those can be twice as fast there.
     if (o.refine_unroll) {
         std::vector<Record> ok;
         for (const auto& c : legal) {
@@ -648,9 +658,15 @@ int tune_core(const conv2d_shape& s, const conv2d_tune_opts& o, Measurer* meas, 
             if (r.status == kOk) ok.push_back(r);
         }
         std::sort(ok.begin(), ok.end(), [](const Record& a, const Record& b) { return a.ms < b.ms; });
-        if (ok.size() > 10) ok.resize(10);
+        std::vector<Record> chosen;
+        int n_matrix = 0;
+        for (const auto& r : ok) {
+            const bool m = o.unroll == 1 && matrix_with_unroll(s, r.c) && n_matrix < 10;
+            if (m) ++n_matrix;
+            if (m || &r < &ok[0] + 10) chosen.push_back(r);
+        }
         std::vector<conv2d_config> extra;
-        for (const auto& r : ok)
+        for (const auto& r : chosen)
             for (int u : {0, 1, 2, 4}) {
                 conv2d_config c2 = r.c;
                 c2.unroll = u;

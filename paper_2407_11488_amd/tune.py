@@ -2,7 +2,7 @@
 
 One shape:
     python -m paper_2407_11488_amd.tune --shape 4096 4096 17 17 [--results PATH]
-        [--winners PATH] [--reps 20] [--retime-reps 200] [--no-flush] [--unroll 1]
+        [--winners PATH] [--reps 20] [--retime-reps 200] [--no-flush] [--unroll 2]
         [--no-refine-unroll] [--max-configs N] [--json OUT]
 
 Filter-size sweep (each shape tuned, then compared with a reference shape's
@@ -146,7 +146,8 @@ def main(argv=None) -> int:
     ap.add_argument("--retime-reps", type=int, default=200)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--no-flush", action="store_true")
-    ap.add_argument("--unroll", type=int, default=1)
+    ap.add_argument("--unroll", type=int, default=2,
+                    help="unroll of every point of the sweep (2: even tiles run on the matrix cores; 1: none does)")
     ap.add_argument("--no-refine-unroll", action="store_true")
     ap.add_argument("--max-configs", type=int, default=0)
     ap.add_argument("--threads", type=int, default=0)
