@@ -76,6 +76,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 #else
 #define CONV_HAVE_MFMA 0
 #endif
+// Where the matrix path is possible but slower (Geo::PAYS_LDS, PAYS_GLOBAL), the
+// plain one runs; the CPU harness takes it wherever it is possible.
+#if defined(CONV_EMULATED_MFMA)
+#define CONV_MATRIX_PAYS true
+#else
+#define CONV_MATRIX_PAYS (LDS ? PAYS_LDS : PAYS_GLOBAL)
+#endif
 
 // At least two waves per SIMD on the matrix path: with more than 256 registers
 // to hand out, the compiler keeps the accumulators of matrix instructions in
@@ -116,13 +123,31 @@ struct Geo {
     static constexpr int LDS_PITCH = (LDS_PITCH0 % 32 == 0) ? LDS_PITCH0 + 4 : LDS_PITCH0;
     static constexpr int LDS_FLOATS = LDS ? LDS_ROWS * LDS_PITCH : 4;
     static constexpr int ROW_UNROLL = UNROLL == 0 ? NROWS : UNROLL;   // 0 = the whole row loop
+    // Where the matrix path is the faster one. With the tile in LDS it is from 3
+    // x 3 on (4 x (9 FMAs) there take 144 cycles plain and 4 * 8 + 20 * 4 = 112
+    // on it, 17 x 17 4624 and 2576), but not for 2 x 2 outputs under a tall
+    // filter, whose rows hold too few interior columns for the load of their
+    // taps (31 x 3 at 4096 x 4096: 55 and 67 us rolled, fully unrolled 75 and 71
+    // but 4.6 and 5.6 at 700 x 700).
+    static constexpr bool PAYS_LDS = TX * TY >= 8 || FH <= 4 * FW;
+    // Without LDS a thread reads its window from global memory row by row, and
+    // small tiles under small filters are bound by those loads, to which the
+    // path adds that of the taps. Measured at 4096 x 4096, plain and matrix: 2 x
+    // 2 outputs 3 x 3 19.5 and 26.3 us, 9 x 9 61 and 73, 17 x 17 172 and 197
+    // (but 297 and 197 fully unrolled, where the taps no longer fit the scalar
+    // registers); 4 x 2 7 x 7 29 and 34, 9 x 9 equal, 11 x 11 61 and 59; 4 x 4
+    // 5 x 5 fully unrolled 20.2 and 22.1, unroll 2 24.0 and 22.2, 31 x 3 61 and
+    // 68, 9 x 9 41 and 32.
+    static constexpr int SIDE = min_(FH, FW);
+    static constexpr bool PAYS_GLOBAL = TX * TY >= 16 && SIDE >= 9   ? true
+                                        : TX >= 4 && TY >= 4         ? UNROLL != 0 && FH <= 4 * FW
+                                        : TX * TY >= 8               ? SIDE >= 11
+                                                                     : SIDE >= 15 && UNROLL == 0;
     // Matrix path (see MatrixRows): whole waves, output tiles of whole 2 x 2
     // blocks, a filter with interior taps, and a row loop that is not asked to
-    // stay rolled (unroll 1 keeps one row's plain FMAs as its body). From 3 x 3
-    // on it is never the slower one: 4 x (9 FMAs) there take 144 cycles plain
-    // and 4 * 8 + 20 * 4 = 112 here, 17 x 17 4624 and 2576.
+    // stay rolled (unroll 1 keeps one row's plain FMAs as its body).
     static constexpr bool MATRIX = CONV_HAVE_MFMA && UNROLL != 1 && TX % 2 == 0 && TY % 2 == 0 && NT % 64 == 0 &&
-                                   FH >= 3 && FW >= 3;
+                                   FH >= 3 && FW >= 3 && CONV_MATRIX_PAYS;
 };
 
 // Filter taps: the module's __constant__ copy, or the filter pointer.

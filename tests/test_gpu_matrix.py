@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 C = pytest.importorskip("paper_2407_11488_amd")
 
 # (block_x, block_y, tile_x, tile_y, use_lds, filter_in_const, unroll)
-CONFIGS = [(16, 16, 4, 4, 1, 0, 0), (32, 8, 4, 2, 1, 0, 4), (64, 1, 2, 2, 0, 1, 2), (16, 4, 8, 8, 1, 1, 4),
+CONFIGS = [(16, 16, 4, 4, 1, 0, 0), (32, 8, 4, 2, 1, 0, 4), (64, 1, 2, 2, 0, 1, 2), (16, 4, 8, 4, 1, 1, 4),
            (128, 2, 2, 8, 0, 0, 2), (64, 4, 8, 2, 0, 0, 0)]
 SMALLEST_UNIT = 2.0 ** -149    # spacing of subnormal FP32 values
 
@@ -26,13 +26,16 @@ def _bits(t):
 
 
 def test_whole_matrix_space_integer_data_bitwise():
-    """Every configuration that takes the path at unroll 2, on a ragged shape
-    that spans several tiles: integer data makes every partial sum exact."""
-    H, W, fh, fw = 70, 45, 5, 3
+    """Every configuration that can take the path at unroll 2, on a ragged shape
+    that spans several tiles: integer data makes every partial sum exact. The
+    filter is large enough that most do take it also without LDS."""
+    H, W, fh, fw = 70, 45, 11, 12
     s = C.shape(H, W, fh, fw)
     every = [c for c in C.conv2d_space(s, 2, -1) if c[2] % 2 == 0 and c[3] % 2 == 0 and c[0] * c[1] % 64 == 0]
     assert len(every) == 576
-    cfgs = [c for c in every if C.conv2d_lds_bytes(fh, fw, c) <= 163840]
+    # without the four that spill: scratch that a queue keeps upsets tests that fill the memory
+    cfgs = [c for c in every if C.conv2d_lds_bytes(fh, fw, c) <= 163840 and
+            not (c[0] * c[1] == 1024 and c[2] * c[3] == 64 and c[4] == 0)]
     precompile(C, s, cfgs, VEC, VEC)
     inp, f = datagen.conv_problem(H, W, fh, fw, kind="int", seed_in=8, seed_f=9)
     ref, _ = oracle.conv2d_f64(inp, f)
@@ -52,7 +55,7 @@ def test_filters_equal_the_reference(fh, fw):
     """Filters with 2 to 62 interior columns, uniform data, ragged images."""
     H, W = 71, 205
     s = C.shape(H, W, fh, fw)
-    cfgs = [c[:6] + (u,) for c in CONFIGS for u in (c[6], 2) if (u != 0 or fh * fw <= 400) and
+    cfgs = [c[:6] + (u,) for c in CONFIGS for u in (c[6], 2) if (u != 0 or (fh <= 31 and fh * fw <= 400)) and
             C.conv2d_config_check(s, c) == 0]
     precompile(C, s, cfgs, VEC, VEC)
     inp, f = datagen.conv_problem(H, W, fh, fw, seed_in=30 + fh, seed_f=40 + fw)
