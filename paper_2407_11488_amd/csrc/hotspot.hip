@@ -123,14 +123,15 @@ static __device__ __forceinline__ float cell_sum(float north, float south, float
 {
     return __builtin_fmaf(ky, north + south, __builtin_fmaf(kx, west + east, src));
 }
-// Tiles of up to 8 cells take the second part in place, after all sums. Left to
+// Tiles of 4 to 8 cells take the second part in place, after all sums. Left to
 // the compiler, the FMA writes the sum's register, and a step copies its cells:
 // 8 of the 52 vector instructions of a step of 8 cells. 60 steps at 4096 x 4096
-// took (32,16,2,4,8) 363.6 us (now 353.0), at 2048 x 2048 130.1 (127.5), 20
+// took (32,16,2,4,8) 360.7 us (now 354.0), at 2048 x 2048 130.1 (127.5), 20
 // steps at 1000 x 1501 28.0 (27.6). Larger tiles would keep too many sums: 60
 // steps of 4 x 4 cells took 408 us that way and take 377 as the compiler orders
-// them.
-#define HS_IN_PLACE (HS_TX * HS_TY <= 8)
+// them. Smaller ones have little to copy and wait for the fences below: 8 steps
+// of 2 x 1 cells, (32,16,2,1,4), took 142 us in place and take 135.
+#define HS_IN_PLACE (HS_TX * HS_TY >= 4 && HS_TX * HS_TY <= 8)
 static __device__ __forceinline__ float cell_add(float t, float ka, float sum)
 {
 #if HS_IN_PLACE && defined(__AMDGCN__)
