@@ -169,7 +169,9 @@ int conv2d_cache_store(const char *path, const char *arch, conv2d_shape s,
  * recent) when it is legal for this shape, else the cache's entry for any
  * shape, (-1, -1, 0, 0), else the default configuration (below 2^22 outputs
  * the entry for any shape comes before a winner of the filter that was tuned at
- * 2^22 outputs or more); the environment variable CONV2D_FORCE_CONFIG
+ * 2^22 outputs or more, and at any size before one whose tiles would lie mostly
+ * outside the image; images of few columns or rows take small tiles in its
+ * place); the environment variable CONV2D_FORCE_CONFIG
  * ("bx,by,tx,ty,lds,const,unroll") overrides them all. Compiles (or loads from
  * the code-object cache) and loads the module. The plan owns the module.
  * Source: Section 5 (the convolution benchmark kernel) with a point of the
@@ -227,7 +229,8 @@ int conv2d_fill_uniform(float *d_out, size_t n, uint64_t seed, uint64_t start, v
  * round), else the winners cache entry for 4096x4096 with that filter, else
  * the most recent entry with that filter, else the entry for any shape (with
  * CONV2D_BATCH_BY_SIZE, up to 1536, before a winner of the filter tuned at 2^22
- * outputs or more), else the default; the
+ * outputs or more; in every case before an entry whose tiles would lie mostly
+ * outside the filter's images), else the default; the
  * filter is always read through its pointer. The problems sharing a filter size and
  * configuration form a group, run as one kernel over the group's tiles (a
  * workgroup per tile, the tiles of each image in row order, XCD-contiguous

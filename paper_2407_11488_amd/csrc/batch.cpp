@@ -187,47 +187,69 @@ int size_bucket(int out_h, int out_w)
     return b;
 }
 
-// The configuration the batched path uses for a filter size: with a size
+// The configurations the batched path uses for a filter size: with a size
 // bucket (> 0), the bucket's entry, else the filter's whole-batch entry;
 // without (bucket 0), the whole-batch entry, else the entry of the bucket
 // `fallback_bucket`; then the 4096x4096 winner or the filter's most recent
 // entry (small buckets: the entry for any shape before a winner at 2^22 outputs
 // or more), else the entry for any shape, else the default. The filter is read
 // through its pointer.
-static conv2d_config lookup_batch_config(const DeviceInfo& dev, const std::string& wp, int fh, int fw, int bucket,
+static BatchConfigs lookup_batch_configs(const DeviceInfo& dev, const std::string& wp, int fh, int fw, int bucket,
                                          int fallback_bucket = 0)
 {
     const conv2d_shape tuned_shape{4096, 4096, fh, fw};
+    BatchConfigs r;
     conv2d_config cfg{};
     auto entry = [&](int b) { return cache_lookup(wp, dev.arch, batch_key(fh, fw, b), &cfg, nullptr) == CONV2D_OK; };
     bool found = bucket > 0 ? entry(bucket) || entry(0) : entry(0) || (fallback_bucket > 0 && entry(fallback_bucket));
     const bool small = bucket > 0 && bucket <= 3;   // sides up to 1536: below kSmallOutputs
+    r.any = cache_lookup_any(wp, dev, fh, fw);
     if (!found) {
-        conv2d_config near{};   // the same filter's plain entry
         conv2d_shape from{};
-        const bool have_near = cache_lookup_filter(wp, dev.arch, fh, fw, tuned_shape, &near, &from) == CONV2D_OK;
-        if (small && !(have_near && tuned_small(from)))
-            found = cache_lookup_any(wp, dev, tuned_shape, &cfg) == CONV2D_OK;
-        if (!found && have_near) {
-            cfg = near;
-            found = true;
-        }
+        const bool near = cache_lookup_filter(wp, dev.arch, fh, fw, tuned_shape, &cfg, &from) == CONV2D_OK;
+        if (r.any.found && !(near && !(small && !tuned_small(from)))) cfg = r.any.configs[0];
+        else if (!near) conv2d_default_config(&cfg);
     }
-    if (!found) found = cache_lookup_any(wp, dev, tuned_shape, &cfg) == CONV2D_OK;
-    if (!found) conv2d_default_config(&cfg);
     clear_error();
     cfg.filter_in_const = 0;  // each problem has its own filter
+    for (auto& c : r.any.configs) c.filter_in_const = 0;
     if (conv2d_config_check(tuned_shape, &cfg, dev.lds_limit) != CONV2D_OK) {
         conv2d_default_config(&cfg);
         cfg.filter_in_const = 0;
         clear_error();
     }
-    return cfg;
+    r.main = cfg;
+    return r;
 }
 
-conv2d_config batch_config_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket)
+BatchConfigs batch_configs_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket)
 {
-    return lookup_batch_config(dev, winners_path_or_default(nullptr), fh, fw, bucket, fallback_bucket);
+    return lookup_batch_configs(dev, winners_path_or_default(nullptr), fh, fw, bucket, fallback_bucket);
+}
+
+conv2d_config BatchConfigs::pick(const conv2d_shape& s) const
+{
+    if (!any.found) return main;
+    const conv2d_config c = any.pick(s);
+    Covered c_main, c_any;
+    c_main.add(main, s.out_h, s.out_w);
+    c_any.add(c, s.out_h, s.out_w);
+    return wasteful(c_main, c_any) ? c : main;
+}
+
+conv2d_config BatchConfigs::pick(const std::vector<conv2d_shape>& images) const
+{
+    if (!any.found) return main;
+    auto total = [&](const conv2d_config& c) {
+        Covered n;
+        for (const auto& s : images) n.add(c, s.out_h, s.out_w);
+        return n;
+    };
+    // Of the picks for one image or another, the one that covers least in all.
+    const conv2d_config* best = &any.configs[0];
+    for (const auto& c : any.configs)
+        if (total(*best).waves >= 1.5 * total(c).waves) best = &c;
+    return wasteful(total(main), total(*best)) ? *best : main;
 }
 
 // The batched kernel's problems have rows of every alignment; it takes the
@@ -281,22 +303,28 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     // gives each problem its size bucket's entry (the buckets of a filter that
     // share a configuration share a kernel).
     using Key = std::pair<std::pair<int, int>, std::string>;
-    std::map<std::tuple<int, int, int>, conv2d_config> chosen;
+    const bool by_size = (flags & CONV2D_BATCH_BY_SIZE) != 0;
+    std::map<std::pair<int, int>, std::vector<conv2d_shape>> of_filter;
+    if (!by_size)
+        for (int i = 0; i < n; ++i) of_filter[{shapes[i].filt_h, shapes[i].filt_w}].push_back(shapes[i]);
+    std::map<std::tuple<int, int, int>, BatchConfigs> configs;
+    std::map<std::tuple<int, int, int>, conv2d_config> shared;   // not by size: one per filter and fallback bucket
     std::map<Key, std::vector<int>> by_kernel;
     std::map<Key, conv2d_config> kernel_cfg;
     for (int i = 0; i < n; ++i) {
-        const auto bk = std::make_tuple(shapes[i].filt_h, shapes[i].filt_w, size_bucket(shapes[i].out_h, shapes[i].out_w));
-        auto it = chosen.find(bk);
-        if (it == chosen.end()) {
-            const int bucket = std::get<2>(bk);
-            const conv2d_config c = (flags & CONV2D_BATCH_BY_SIZE)
-                                        ? batch_config_for(b->dev, shapes[i].filt_h, shapes[i].filt_w, bucket, 0)
-                                        : batch_config_for(b->dev, shapes[i].filt_h, shapes[i].filt_w, 0, bucket);
-            it = chosen.emplace(bk, c).first;
+        const conv2d_shape& s = shapes[i];
+        const int bucket = size_bucket(s.out_h, s.out_w);
+        const auto bk = std::make_tuple(s.filt_h, s.filt_w, bucket);
+        auto it = configs.find(bk);
+        if (it == configs.end()) {
+            it = configs.emplace(bk, by_size ? batch_configs_for(b->dev, s.filt_h, s.filt_w, bucket, 0)
+                                             : batch_configs_for(b->dev, s.filt_h, s.filt_w, 0, bucket)).first;
+            if (!by_size) shared[bk] = it->second.pick(of_filter[{s.filt_h, s.filt_w}]);
         }
-        const Key key{{shapes[i].filt_h, shapes[i].filt_w}, config_str(it->second)};
+        const conv2d_config c = by_size ? it->second.pick(s) : shared[bk];
+        const Key key{{s.filt_h, s.filt_w}, config_str(c)};
         by_kernel[key].push_back(i);
-        kernel_cfg[key] = it->second;
+        kernel_cfg[key] = c;
     }
     std::vector<Key> keys;
     for (auto& kv : by_kernel) keys.push_back(kv.first);
@@ -777,7 +805,7 @@ extern "C" int conv2d_batch_tune(int n, const conv2d_shape* shapes, const conv2d
     std::vector<std::pair<conv2d_shape, conv2d_config>> to_compile;
     for (const auto& kv : groups) {
         const int fh = std::get<0>(kv.first), fw = std::get<1>(kv.first), bk = std::get<2>(kv.first);
-        std::vector<conv2d_config> c{lookup_batch_config(dev, wp, fh, fw, bk)};
+        std::vector<conv2d_config> c{lookup_batch_configs(dev, wp, fh, fw, bk).main};
         for (const auto& x : sweep_candidates(dev, rdir, fh, fw, o.candidates)) {
             bool seen = false;
             for (const auto& e : c) seen = seen || config_equal(e, x);

@@ -112,6 +112,13 @@ struct Geometry {
     int tiles_x = 0, tiles_y = 0, n_tiles = 0, threads = 0;
 };
 Geometry geometry(int out_h, int out_w, const conv2d_config& c);
+// Outputs that a configuration covers on an image, those outside it included:
+// by its waves (those wholly outside leave at once), and by its tiles, for which
+// a workgroup holds LDS and registers.
+struct Covered {
+    double waves = 0, tiles = 0;
+    void add(const conv2d_config& c, int out_h, int out_w);
+};
 // Largest number of output rows per launch so that the input band stays below
 // 2^31 bytes (buffer offsets are 32-bit).
 int band_rows(const conv2d_shape& s);
@@ -148,6 +155,25 @@ int launch_count_mismatch(const float* a, const float* b, size_t n, unsigned* d_
                           hipStream_t stream);
 int launch_flush(float* d, size_t n, hipStream_t stream);
 
+// The winners-cache shape of the configuration for any size and any filter: a
+// compromise over both, for shapes that have no better entry.
+constexpr conv2d_shape kAnyShape{-1, -1, 0, 0};
+// That entry for a filter (if it is legal there), and what thin images, which
+// its tiles cover badly, take in its place.
+struct AnyShape {
+    bool found = false;
+    std::vector<conv2d_config> configs;   // the entry, then those for thin images
+    conv2d_config pick(const conv2d_shape& s) const;
+};
+AnyShape cache_lookup_any(const std::string& path, const DeviceInfo& dev, int fh, int fw);
+// Does an entry that covers `c` give way to a pick of AnyShape that covers
+// `than`? Per covered output the pick takes up to a third longer (2 x 2 outputs a
+// thread against 4 x 2, 4 x 2 against a 4096 x 4096 winner's 4 x 4).
+inline bool wasteful(const Covered& c, const Covered& than)
+{
+    return c.waves >= 1.5 * than.waves || c.tiles >= 2.0 * than.tiles;
+}
+
 // ---------------------------------------------------------------- batched kernels
 // Mirror of the batched kernel's ConvDesc (conv2d_direct.hip, CONV_BATCH=1).
 struct ConvDesc {
@@ -164,11 +190,20 @@ static_assert(sizeof(ConvDesc) == 48, "descriptor layout must match the kernel")
 
 // Size bucket (1..CONV2D_SIZE_BUCKETS) of a problem for the batched path.
 int size_bucket(int out_h, int out_w);
-// The batched kernel's configuration for filter fh x fw from the winners
-// cache: size bucket `bucket`'s entry, else the whole-batch entry (bucket 0:
-// the whole-batch entry, else bucket `fallback_bucket`'s), else the 4096x4096
-// winner, else the default; filter through its pointer.
-conv2d_config batch_config_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket = 0);
+// The batched kernel's configurations for filter fh x fw from the winners
+// cache. main: size bucket `bucket`'s entry, else the whole-batch entry (bucket
+// 0: the whole-batch entry, else bucket `fallback_bucket`'s), else the 4096x4096
+// winner or the entry for any shape, else the default; any: what the entry for
+// any shape gives for each kind of image, if the cache has it. The filter is
+// read through its pointer.
+struct BatchConfigs {
+    conv2d_config main{};
+    AnyShape any;
+    // For one image, and for images that share a kernel.
+    conv2d_config pick(const conv2d_shape& s) const;
+    conv2d_config pick(const std::vector<conv2d_shape>& images) const;
+};
+BatchConfigs batch_configs_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket);
 // Compiles and loads the batched kernel of a configuration (the rolled row
 // loop replaces one that spills; cfg->unroll then becomes 1).
 int batch_module(const DeviceInfo& dev, int fh, int fw, conv2d_config* cfg, Module* m);
@@ -212,11 +247,6 @@ int cache_store(const std::string& path, const std::string& arch, const conv2d_s
 // most recent entry of any shape with that filter size. *from: its shape.
 int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
                         const conv2d_shape& prefer, conv2d_config* c, conv2d_shape* from = nullptr);
-// The winners-cache shape of the configuration for any size and any filter: a
-// compromise over both, for shapes that have no better entry. It must be legal
-// for s.
-constexpr conv2d_shape kAnyShape{-1, -1, 0, 0};
-int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2d_shape& s, conv2d_config* c);
 // Outputs below which that entry is preferred to the winner of the filter at
 // another size. The shipped entry has 128 x 16 outputs a workgroup: up to
 // about 8 waves per SIMD of it. Winners at 4096 x 4096 have larger tiles that

@@ -245,7 +245,7 @@ extern "C" int conv2d_plan(conv2d_plan_t* plan, conv2d_shape s, const conv2d_con
         std::string wp = env_str("CONV2D_WINNERS");
         if (wp.empty()) wp = winners_default_path();
         bool stale = false;
-        conv2d_config own{}, near{}, any{};
+        conv2d_config own{}, near{};
         conv2d_shape from{};
         const bool have_own = cache_lookup(wp, dev.arch, s, &own, &ms, &stale) == CONV2D_OK;
         // The same filter's winner for another shape (4096 x 4096 first).
@@ -254,16 +254,24 @@ extern "C" int conv2d_plan(conv2d_plan_t* plan, conv2d_shape s, const conv2d_con
                                                    conv2d_shape{4096, 4096, s.filt_h, s.filt_w}, &near,
                                                    &from) == CONV2D_OK &&
                                conv2d_config_check(s, &near, dev.lds_limit) == CONV2D_OK;
-        const bool have_any = !have_own && cache_lookup_any(wp, dev, s, &any) == CONV2D_OK;
-        const bool small = (long long)s.out_h * s.out_w < kSmallOutputs;
+        const AnyShape a = have_own ? AnyShape{} : cache_lookup_any(wp, dev, s.filt_h, s.filt_w);
+        const conv2d_config any = a.found ? a.pick(s) : conv2d_config{};
+        bool gives_way = false;   // near to any
+        if (have_near && a.found) {
+            Covered c_near, c_any;
+            c_near.add(near, s.out_h, s.out_w);
+            c_any.add(any, s.out_h, s.out_w);
+            const bool small = (long long)s.out_h * s.out_w < kSmallOutputs && !tuned_small(from);
+            gives_way = small || wasteful(c_near, c_any);
+        }
         if (have_own) {
             p->cfg = own;
             p->source = stale ? 3 : 1;
-        } else if (have_near && !(have_any && small && !tuned_small(from))) {
+        } else if (have_near && !gives_way) {
             p->cfg = near;
             p->source = 4;
-        } else if (have_any) {
-            // Small, or a filter nobody tuned: against the default, the entry
+        } else if (a.found) {
+            // Against the default, where a filter has no entry at all, the entry
             // for any shape takes 0.42 of the time (geometric mean of 14 filters from
             // 1 x 1 to 45 x 17 at 128 x 128 to 3000 x 2500; at worst 0.74) and
             // stays within 2 % of the best of 14 candidates.

@@ -165,25 +165,25 @@ public:
             // built up front (buckets that share a configuration share one).
             if (!o_.serial_plain) {
                 const auto bkey = std::make_tuple(s.filt_h, s.filt_w, size_bucket(s.out_h, s.out_w));
-                auto it = kernel_of_bucket_.find(bkey);
-                if (it == kernel_of_bucket_.end()) {
-                    const conv2d_config c = batch_config_for(dev_, s.filt_h, s.filt_w, std::get<2>(bkey), 0);
-                    const auto ckey = std::make_pair(std::make_pair(s.filt_h, s.filt_w), config_str(c));
-                    auto jt = kernel_of_cfg_.find(ckey);
-                    if (jt == kernel_of_cfg_.end()) {
-                        FilterKernel fk;
-                        fk.fh = s.filt_h;
-                        fk.fw = s.filt_w;
-                        fk.cfg = c;
-                        rc = batch_module(dev_, s.filt_h, s.filt_w, &fk.cfg, &fk.mod);
-                        if (rc) return rc;
-                        kernels_.push_back(fk);
-                        jt = kernel_of_cfg_.emplace(ckey, (int)kernels_.size() - 1).first;
-                    }
-                    it = kernel_of_bucket_.emplace(bkey, jt->second).first;
+                auto it = configs_of_bucket_.find(bkey);
+                if (it == configs_of_bucket_.end())
+                    it = configs_of_bucket_.emplace(bkey, batch_configs_for(dev_, s.filt_h, s.filt_w,
+                                                                            std::get<2>(bkey), 0)).first;
+                const conv2d_config chosen = it->second.pick(s);
+                const auto ckey = std::make_pair(std::make_pair(s.filt_h, s.filt_w), config_str(chosen));
+                auto jt = kernel_of_cfg_.find(ckey);
+                if (jt == kernel_of_cfg_.end()) {
+                    FilterKernel fk;
+                    fk.fh = s.filt_h;
+                    fk.fw = s.filt_w;
+                    fk.cfg = chosen;
+                    rc = batch_module(dev_, s.filt_h, s.filt_w, &fk.cfg, &fk.mod);
+                    if (rc) return rc;
+                    kernels_.push_back(fk);
+                    jt = kernel_of_cfg_.emplace(ckey, (int)kernels_.size() - 1).first;
                 }
-                req_[i].kernel = it->second;
-                const conv2d_config& c = kernels_[(size_t)it->second].cfg;
+                req_[i].kernel = jt->second;
+                const conv2d_config& c = kernels_[(size_t)jt->second].cfg;
                 max_tiles_per_req = std::max(max_tiles_per_req, (size_t)geometry(s.out_h, s.out_w, c).n_tiles);
             }
         }
@@ -501,7 +501,7 @@ private:
     DeviceInfo dev_;
     std::vector<Req> req_;
     std::vector<FilterKernel> kernels_;
-    std::map<std::tuple<int, int, int>, int> kernel_of_bucket_;
+    std::map<std::tuple<int, int, int>, BatchConfigs> configs_of_bucket_;
     std::map<std::pair<std::pair<int, int>, std::string>, int> kernel_of_cfg_;
     std::map<std::pair<int, int>, conv2d_config> direct_cfg_;
     std::map<std::tuple<int, int, int, int>, Module> direct_;

@@ -116,13 +116,49 @@ bool tuned_small(const conv2d_shape& e)
     return e.out_h == 0 ? e.out_w <= 3 : (long long)e.out_h * e.out_w < kSmallOutputs;
 }
 
-int cache_lookup_any(const std::string& path, const DeviceInfo& dev, const conv2d_shape& s, conv2d_config* c)
+AnyShape cache_lookup_any(const std::string& path, const DeviceInfo& dev, int fh, int fw)
 {
+    AnyShape r;
+    const conv2d_shape s{4096, 4096, fh, fw};
     conv2d_config any{};
-    int rc = cache_lookup(path, dev.arch, kAnyShape, &any, nullptr);
-    if (!rc) rc = conv2d_config_check(s, &any, dev.lds_limit);
-    if (!rc) *c = any;
-    return rc;
+    if (cache_lookup(path, dev.arch, kAnyShape, &any, nullptr) != CONV2D_OK ||
+        conv2d_config_check(s, &any, dev.lds_limit) != CONV2D_OK)
+        return r;
+    r.found = true;
+    r.configs = {any, {16, 16, 2, 2, 1, 0, 4}, {128, 2, 4, 1, 0, 0, 4}, {128, 2, 4, 2, 1, 0, 4},
+                 {64, 4, 4, 2, 1, 0, 4}};
+    for (auto& c : r.configs)
+        if (conv2d_config_check(s, &c, dev.lds_limit) != CONV2D_OK) c = any;
+    return r;
+}
+
+void Covered::add(const conv2d_config& c, int out_h, int out_w)
+{
+    auto area = [&](int w, int h) { return (double)w * ((out_w - 1) / w + 1) * h * ((out_h - 1) / h + 1); };
+    const int lanes = std::min(c.block_x, 64);
+    waves += area(lanes * c.tile_x, 64 / lanes * c.tile_y);
+    tiles += area(c.block_x * c.tile_x, c.block_y * c.tile_y);
+}
+
+// The entry (as shipped, waves of 128 x 4 outputs) unless the image is thin.
+// Few columns take waves of 32 x 8: measured over 12 filters from 3 x 3 to 31 x
+// 31, 1 x 9 and 9 x 1 (geometric means, the entry = 1; 11 x 11 in us),
+// 1,000,000 x 1 0.33 (301 -> 89), 60,000 x 16 0.44 (20.7 -> 7.8), 15,000 x 64
+// 0.80; at 80 columns, 1.33 times as much covered, both are as fast. One or two
+// rows are read without LDS, since a tile's outputs share few input rows: one
+// of 1,000,000 0.51 (18.8 -> 8.8), two of 500,000 0.71; but two rows under 11 x 11
+// and more take tiles of 256 x 8 in LDS (15 x 15, two of 2,500,000: 67.6 -> 55.7).
+// Three or four rows take tiles of 512 x 4 in LDS: 0.93 and 0.95; six rows would
+// take 1.2.
+conv2d_config AnyShape::pick(const conv2d_shape& s) const
+{
+    Covered entry, narrow;
+    entry.add(configs[0], s.out_h, s.out_w);
+    narrow.add(configs[1], s.out_h, s.out_w);
+    if (entry.waves >= 1.5 * narrow.waves) return configs[1];
+    if (s.out_h > 4) return configs[0];
+    if (s.out_h > 2) return configs[3];
+    return configs[s.out_h == 2 && std::min(s.filt_h, s.filt_w) >= 11 ? 4 : 2];
 }
 
 int cache_store(const std::string& path, const std::string& arch, const conv2d_shape& s,
