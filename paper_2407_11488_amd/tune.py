@@ -22,6 +22,9 @@ The batched path's configurations chosen in context (each group's
 candidates timed as the whole 64-problem batch, the other groups held,
 coordinate descent; appended as the (0, 0, fh, fw) winners):
     python -m paper_2407_11488_amd.tune --batch-context [--candidates 24] [--rounds 2]
+The entry for any shape, (-1, -1, 0, 0), that untuned filters and small images
+take (13 configurations over 14 filters at five sizes; lowest geometric mean):
+    python -m paper_2407_11488_amd.tune --any-shape
 The server's stream count and batch-size cap (streams 1-8 x caps 1-256, each
 serving one Poisson trace at a fraction of serial capacity; lowest p99 wins),
 stored in tuned/serve_params.json:
@@ -166,6 +169,7 @@ def main(argv=None) -> int:
     ap.add_argument("--buckets", action="store_true",
                     help="batched kernels per filter size and size bucket, on a sample of served shapes")
     ap.add_argument("--sample", type=int, default=160)
+    ap.add_argument("--any-shape", action="store_true", help="the winners cache's entry for any shape")
     ap.add_argument("--serving", action="store_true",
                     help="the server's stream count and batch-size cap, by p99 on a trace of its own")
     ap.add_argument("--rate", type=float, default=0.8, help="--serving: load as a fraction of serial capacity")
@@ -176,6 +180,10 @@ def main(argv=None) -> int:
     if a.serving:
         from . import workloads
         emit(workloads.tune_serving(a.rate, a.duration), a.json)
+        return 0
+    if a.any_shape:
+        from . import workloads
+        emit(workloads.any_shape_tune(winners=a.winners), a.json)
         return 0
     if a.batch_context:
         from . import workloads

@@ -279,6 +279,87 @@ def batch_context_tune(n: int = 64, candidates: int = 24, rounds: int = 2, reps:
             "candidates": candidates, "rounds": rounds, "stored": bool(store)}
 
 
+# Problems and candidates of any_shape_tune: filters without winners of their
+# own, rectangles among them, under small to middling images.
+ANY_FILTERS = ((1, 1), (2, 2), (1, 9), (9, 1), (3, 7), (5, 11), (11, 11), (12, 6), (13, 13), (16, 16), (21, 21),
+               (25, 25), (33, 33), (45, 17))
+ANY_SIZES = ((128, 128), (300, 260), (700, 900), (1400, 1200), (3000, 2500))
+ANY_CANDIDATES = ((32, 8, 4, 2, 1, 0, 2), (32, 8, 4, 2, 1, 0, 4), (16, 16, 4, 2, 1, 0, 2), (16, 8, 4, 2, 1, 0, 2),
+                  (16, 4, 4, 2, 1, 0, 2), (32, 4, 4, 2, 1, 0, 2), (32, 16, 4, 2, 1, 0, 2), (16, 16, 8, 2, 1, 0, 2),
+                  (32, 8, 4, 4, 1, 0, 2), (64, 4, 4, 2, 1, 0, 2), (64, 4, 4, 4, 0, 0, 2), (64, 4, 4, 4, 1, 0, 2),
+                  (32, 2, 4, 4, 1, 0, 2))
+
+
+def any_shape_tune(filters=ANY_FILTERS, sizes=ANY_SIZES, candidates=ANY_CANDIDATES, tie_rel: float = 0.005,
+                   winners: str = WINNERS, store: bool = True, log=None) -> dict:
+    """The winners cache's entry for any shape, (-1, -1, 0, 0): the candidate
+    with the lowest geometric mean, over every filter on every size, of its
+    time over the fastest candidate's. Each is run as a plan back to back over
+    three copies of the data (its outputs equal to the reference kernel's bit
+    for bit), the better of two timings counting; the current entry stays
+    within tie_rel of the best. The stored ms is the geometric mean time. The
+    default configuration is timed beside them."""
+    import math
+    torch = _torch()
+    from .api import Plan, reference
+    say = log or (lambda m: print(m, file=sys.stderr, flush=True))
+    st = torch.cuda.current_stream()
+    default = B.conv2d_default_config().tuple()
+    ms = {}
+    for fh, fw in filters:
+        for H, W in sizes:
+            ins = [torch.empty((H + fh - 1, W + fw - 1), dtype=torch.float32, device="cuda") for _ in range(3)]
+            filt = torch.empty((fh, fw), dtype=torch.float32, device="cuda")
+            for k, x in enumerate(ins + [filt]):
+                B.conv2d_fill_uniform(x.data_ptr(), x.numel(), 40 + k, 0, st.cuda_stream)
+            outs = [torch.empty((H, W), dtype=torch.float32, device="cuda") for _ in ins]
+            want = reference(ins[0], filt).view(torch.int32)
+            for c in candidates + (default,):
+                plan = Plan(H, W, fh, fw, config=c)
+                if not torch.equal(plan(ins[0], filt, out=outs[0]).view(torch.int32), want):
+                    raise RuntimeError(f"{c} differs from the reference kernel on {H}x{W} under {fh}x{fw}")
+                args = [(plan.handle, x.data_ptr(), filt.data_ptr(), o.data_ptr(), st.cuda_stream)
+                        for x, o in zip(ins, outs)]
+
+                def timed(n):
+                    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    e0.record(st)
+                    for k in range(n):
+                        B.lib.conv2d_run(*args[k % 3])
+                    e1.record(st)
+                    torch.cuda.synchronize()
+                    return e0.elapsed_time(e1) / n
+                n = max(20, int(4.0 / timed(20)))
+                ms[(fh, fw, H, W), c] = min(timed(n), timed(n))
+                plan.close()
+        say(f"[any shape] {fh} x {fw} done")
+    problems = sorted({p for p, _ in ms})
+    best = {p: min(ms[p, c] for c in candidates) for p in problems}
+
+    def gmean(v):
+        return math.exp(sum(map(math.log, v)) / len(v))
+    to_best = {c: [ms[p, c] / best[p] for p in problems] for c in candidates}
+    mean = {c: gmean(v) for c, v in to_best.items()}
+    chosen = min(candidates, key=lambda c: mean[c])
+    arch = torch.cuda.get_device_properties(torch.cuda.current_device()).gcnArchName.split(":")[0]
+    now = B.conv2d_cache_lookup(winners, arch, B.shape(-1, -1, 0, 0))
+    if now is not None and mean.get(now[0].tuple(), math.inf) <= mean[chosen] * (1.0 + tie_rel):
+        chosen = now[0].tuple()
+    chosen_ms = gmean([ms[p, chosen] for p in problems])
+    if store:
+        B.conv2d_cache_store(winners, arch, B.shape(-1, -1, 0, 0), chosen, chosen_ms)
+    to_default = [ms[p, chosen] / ms[p, default] for p in problems]
+    return {"workload": f"entry for any shape, {len(filters)} filters x {len(sizes)} sizes",
+            "chosen": list(chosen), "gmean_ms": round(chosen_ms, 6),
+            "to_best": {"gmean": round(mean[chosen], 4), "worst": round(max(to_best[chosen]), 3),
+                        "worst_problem": list(problems[to_best[chosen].index(max(to_best[chosen]))])},
+            "to_default": {"gmean": round(gmean(to_default), 4), "worst": round(max(to_default), 3)},
+            "candidates": [{"config": list(c), "gmean": round(mean[c], 4), "worst": round(max(to_best[c]), 3)}
+                           for c in sorted(candidates, key=lambda c: mean[c])],
+            "chosen_ms": {"x".join(map(str, p)): round(ms[p, chosen], 5) for p in problems},
+            "best_ms": {"x".join(map(str, p)): round(best[p], 5) for p in problems}, "stored": bool(store)}
+
+
 SWEEP_FILTERS = (3, 5, 7, 9, 15, 17, 31)
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_UNPACKED_TFLOPS = 78.6
