@@ -117,8 +117,9 @@ int hotspot_compile(const hotspot_config *cfg, char *path_out, int path_cap);
  * Table 1 space. */
 int hotspot_plan(hotspot_plan_t *plan, hotspot_shape s, const hotspot_config *cfg);
 
-/* The plan's configuration; *tuned = 1 when it is this grid's winner, 2
- * when it is another grid's, 0 otherwise (given or default).
+/* The plan's configuration; *tuned = 1 when it is this grid's winner, 3 when
+ * that was tuned with an older revision of the kernel source, 2 when it is
+ * another grid's, 0 otherwise (given or default).
  * Source: Table 1 (the parameters of the configuration). */
 int hotspot_plan_config(hotspot_plan_t plan, hotspot_config *cfg, int *tuned);
 

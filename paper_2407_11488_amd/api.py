@@ -192,7 +192,8 @@ class Hotspot:
         self._device = _device()
         self.handle = B.hotspot_plan(self.shape, config)
         self.config, tuned = B.hotspot_plan_config(self.handle)
-        self.source = "given" if config is not None else {1: "tuned", 2: "tuned-other-grid"}.get(tuned, "default")
+        names = {1: "tuned", 2: "tuned-other-grid", 3: "tuned-older-kernel"}
+        self.source = "given" if config is not None else names.get(tuned, "default")
         self._work = None
 
     def __call__(self, temp, power, steps, coeffs, out=None, stream=None):

@@ -535,7 +535,7 @@ struct hotspot_plan_s {
     int device = -1;
     hotspot_shape shape{};
     hotspot_config cfg{};
-    int tuned = 0;
+    int tuned = 0;           // see hotspot_plan_config
     Module mod;
 };
 
@@ -641,9 +641,10 @@ extern "C" int hotspot_plan(hotspot_plan_t* out, hotspot_shape s, const hotspot_
     } else {
         std::string wp = env_str("HOTSPOT_WINNERS");
         if (wp.empty()) wp = hs_winners_default_path();
-        if (hs_cache_lookup(wp, dev.arch, s, &p->cfg, nullptr) == CONV2D_OK &&
+        bool stale = false;
+        if (hs_cache_lookup(wp, dev.arch, s, &p->cfg, &stale) == CONV2D_OK &&
             hotspot_config_check(s, &p->cfg, dev.lds_limit) == CONV2D_OK)
-            p->tuned = 1;
+            p->tuned = stale ? 3 : 1;
         else if (hs_cache_lookup_other(wp, dev.arch, s, dev.lds_limit, &p->cfg) == CONV2D_OK)
             p->tuned = 2;
         else
