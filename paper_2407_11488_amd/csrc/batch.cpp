@@ -17,6 +17,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <set>
 #include <thread>
 #include <tuple>
 
@@ -194,19 +195,19 @@ int size_bucket(int out_h, int out_w)
 // entry (small buckets: the entry for any shape before a winner at 2^22 outputs
 // or more), else the entry for any shape, else the default. The filter is read
 // through its pointer.
-static BatchConfigs lookup_batch_configs(const DeviceInfo& dev, const std::string& wp, int fh, int fw, int bucket,
-                                         int fallback_bucket = 0)
+BatchConfigs batch_configs_for(const Winners& w, const DeviceInfo& dev, int fh, int fw, int bucket,
+                               int fallback_bucket)
 {
     const conv2d_shape tuned_shape{4096, 4096, fh, fw};
     BatchConfigs r;
     conv2d_config cfg{};
-    auto entry = [&](int b) { return cache_lookup(wp, dev.arch, batch_key(fh, fw, b), &cfg, nullptr) == CONV2D_OK; };
+    auto entry = [&](int b) { return cache_lookup(w, batch_key(fh, fw, b), &cfg); };
     bool found = bucket > 0 ? entry(bucket) || entry(0) : entry(0) || (fallback_bucket > 0 && entry(fallback_bucket));
     const bool small = bucket > 0 && bucket <= 3;   // sides up to 1536: below kSmallOutputs
-    r.any = cache_lookup_any(wp, dev, fh, fw);
+    r.any = cache_lookup_any(w, dev, fh, fw);
     if (!found) {
         conv2d_shape from{};
-        const bool near = cache_lookup_filter(wp, dev.arch, fh, fw, tuned_shape, &cfg, &from) == CONV2D_OK;
+        const bool near = cache_lookup_filter(w, fh, fw, tuned_shape, &cfg, &from);
         if (r.any.found && !(near && !(small && !tuned_small(from)))) cfg = r.any.configs[0];
         else if (!near) conv2d_default_config(&cfg);
     }
@@ -222,11 +223,6 @@ static BatchConfigs lookup_batch_configs(const DeviceInfo& dev, const std::strin
     return r;
 }
 
-BatchConfigs batch_configs_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket)
-{
-    return lookup_batch_configs(dev, winners_path_or_default(nullptr), fh, fw, bucket, fallback_bucket);
-}
-
 conv2d_config BatchConfigs::pick(const conv2d_shape& s) const
 {
     if (!any.found) return main;
@@ -234,7 +230,7 @@ conv2d_config BatchConfigs::pick(const conv2d_shape& s) const
     Covered c_main, c_any;
     c_main.add(main, s.out_h, s.out_w);
     c_any.add(c, s.out_h, s.out_w);
-    return wasteful(c_main, c_any) ? c : main;
+    return c_main.waves >= 2.0 * c_any.waves || c_main.tiles >= 2.0 * c_any.tiles ? c : main;
 }
 
 conv2d_config BatchConfigs::pick(const std::vector<conv2d_shape>& images) const
@@ -302,29 +298,52 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     // its problems: a large mixed batch runs best so); CONV2D_BATCH_BY_SIZE
     // gives each problem its size bucket's entry (the buckets of a filter that
     // share a configuration share a kernel).
-    using Key = std::pair<std::pair<int, int>, std::string>;
+    // An image that its entry covers badly (BatchConfigs::pick) gets a kernel of
+    // its own by size, if other images have it anyway or if those that share it
+    // save more than one more kernel costs: its launch and about the run of one tile, 3 us at 3 x 3 and 13 at 31
+    // x 31 (200 images up to 200 under 31 x 31, 7 us saved: 56 us with one kernel,
+    // 76 with two).
+    const Winners winners = plan_winners(b->dev.arch);
     const bool by_size = (flags & CONV2D_BATCH_BY_SIZE) != 0;
+    using Key = std::pair<std::pair<int, int>, std::string>;
+    auto key_of = [&](int i, const conv2d_config& c) { return Key{{shapes[i].filt_h, shapes[i].filt_w}, config_str(c)}; };
     std::map<std::pair<int, int>, std::vector<conv2d_shape>> of_filter;
-    if (!by_size)
-        for (int i = 0; i < n; ++i) of_filter[{shapes[i].filt_h, shapes[i].filt_w}].push_back(shapes[i]);
     std::map<std::tuple<int, int, int>, BatchConfigs> configs;
-    std::map<std::tuple<int, int, int>, conv2d_config> shared;   // not by size: one per filter and fallback bucket
-    std::map<Key, std::vector<int>> by_kernel;
-    std::map<Key, conv2d_config> kernel_cfg;
+    std::map<Key, double> saved_flops;
+    std::set<Key> have;   // kernels of the entries themselves
+    std::vector<const BatchConfigs*> of(n);
     for (int i = 0; i < n; ++i) {
         const conv2d_shape& s = shapes[i];
         const int bucket = size_bucket(s.out_h, s.out_w);
         const auto bk = std::make_tuple(s.filt_h, s.filt_w, bucket);
         auto it = configs.find(bk);
-        if (it == configs.end()) {
-            it = configs.emplace(bk, by_size ? batch_configs_for(b->dev, s.filt_h, s.filt_w, bucket, 0)
-                                             : batch_configs_for(b->dev, s.filt_h, s.filt_w, 0, bucket)).first;
-            if (!by_size) shared[bk] = it->second.pick(of_filter[{s.filt_h, s.filt_w}]);
+        if (it == configs.end())
+            it = configs.emplace(bk, batch_configs_for(winners, b->dev, s.filt_h, s.filt_w, by_size ? bucket : 0,
+                                                       by_size ? 0 : bucket)).first;
+        of[i] = &it->second;
+        if (!by_size) {
+            of_filter[{s.filt_h, s.filt_w}].push_back(s);
+            continue;
         }
-        const conv2d_config c = by_size ? it->second.pick(s) : shared[bk];
-        const Key key{{s.filt_h, s.filt_w}, config_str(c)};
-        by_kernel[key].push_back(i);
-        kernel_cfg[key] = c;
+        have.insert(key_of(i, it->second.main));
+        Covered main, own;
+        const conv2d_config c = it->second.pick(s);
+        main.add(it->second.main, s.out_h, s.out_w);
+        own.add(c, s.out_h, s.out_w);
+        saved_flops[key_of(i, c)] += 2.0 * s.filt_h * s.filt_w * (main.waves - own.waves);
+    }
+    std::map<const BatchConfigs*, conv2d_config> shared;   // not by size: one for all images of a filter
+    if (!by_size)
+        for (const auto& kv : configs)
+            shared[&kv.second] = kv.second.pick(of_filter[{std::get<0>(kv.first), std::get<1>(kv.first)}]);
+    std::map<Key, std::vector<int>> by_kernel;
+    std::map<Key, conv2d_config> kernel_cfg;
+    for (int i = 0; i < n; ++i) {
+        conv2d_config c = by_size ? of[i]->pick(shapes[i]) : shared[of[i]];
+        const double cost = 5e-6 + 1e-8 * shapes[i].filt_h * shapes[i].filt_w;
+        if (by_size && !have.count(key_of(i, c)) && saved_flops[key_of(i, c)] < 65e12 * cost) c = of[i]->main;
+        by_kernel[key_of(i, c)].push_back(i);
+        kernel_cfg[key_of(i, c)] = c;
     }
     std::vector<Key> keys;
     for (auto& kv : by_kernel) keys.push_back(kv.first);
@@ -805,7 +824,7 @@ extern "C" int conv2d_batch_tune(int n, const conv2d_shape* shapes, const conv2d
     std::vector<std::pair<conv2d_shape, conv2d_config>> to_compile;
     for (const auto& kv : groups) {
         const int fh = std::get<0>(kv.first), fw = std::get<1>(kv.first), bk = std::get<2>(kv.first);
-        std::vector<conv2d_config> c{lookup_batch_configs(dev, wp, fh, fw, bk).main};
+        std::vector<conv2d_config> c{batch_configs_for(load_winners(wp, dev.arch), dev, fh, fw, bk).main};
         for (const auto& x : sweep_candidates(dev, rdir, fh, fw, o.candidates)) {
             bool seen = false;
             for (const auto& e : c) seen = seen || config_equal(e, x);

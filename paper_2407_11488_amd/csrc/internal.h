@@ -155,6 +155,17 @@ int launch_count_mismatch(const float* a, const float* b, size_t n, unsigned* d_
                           hipStream_t stream);
 int launch_flush(float* d, size_t n, hipStream_t stream);
 
+// The entries of a winners cache for one arch, in the file's order.
+struct Winner {
+    conv2d_shape shape{};
+    conv2d_config config{};
+    double ms = 0;
+    bool current = false;   // tuned with the current kernel source
+};
+struct Winners {
+    bool readable = false;
+    std::vector<Winner> all;
+};
 // The winners-cache shape of the configuration for any size and any filter: a
 // compromise over both, for shapes that have no better entry.
 constexpr conv2d_shape kAnyShape{-1, -1, 0, 0};
@@ -165,7 +176,7 @@ struct AnyShape {
     std::vector<conv2d_config> configs;   // the entry, then those for thin images
     conv2d_config pick(const conv2d_shape& s) const;
 };
-AnyShape cache_lookup_any(const std::string& path, const DeviceInfo& dev, int fh, int fw);
+AnyShape cache_lookup_any(const Winners& w, const DeviceInfo& dev, int fh, int fw);
 // Does an entry that covers `c` give way to a pick of AnyShape that covers
 // `than`? Per covered output the pick takes up to a third longer (2 x 2 outputs a
 // thread against 4 x 2, 4 x 2 against a 4096 x 4096 winner's 4 x 4).
@@ -203,7 +214,10 @@ struct BatchConfigs {
     conv2d_config pick(const conv2d_shape& s) const;
     conv2d_config pick(const std::vector<conv2d_shape>& images) const;
 };
-BatchConfigs batch_configs_for(const DeviceInfo& dev, int fh, int fw, int bucket, int fallback_bucket);
+BatchConfigs batch_configs_for(const Winners& w, const DeviceInfo& dev, int fh, int fw, int bucket,
+                               int fallback_bucket = 0);
+// The winners cache that plans read: $CONV2D_WINNERS, else the default.
+Winners plan_winners(const std::string& arch);
 // Compiles and loads the batched kernel of a configuration (the rolled row
 // loop replaces one that spills; cfg->unroll then becomes 1).
 int batch_module(const DeviceInfo& dev, int fh, int fw, conv2d_config* cfg, Module* m);
@@ -239,14 +253,15 @@ bool append_line(const std::string& path, const std::string& line);
 
 // ---------------------------------------------------------------- winners cache
 std::string winners_default_path();
-int cache_lookup(const std::string& path, const std::string& arch, const conv2d_shape& s,
-                 conv2d_config* c, double* ms, bool* stale = nullptr);
+Winners load_winners(const std::string& path, const std::string& arch);
+bool cache_lookup(const Winners& w, const conv2d_shape& s, conv2d_config* c, double* ms = nullptr,
+                  bool* stale = nullptr);
 int cache_store(const std::string& path, const std::string& arch, const conv2d_shape& s,
                 const conv2d_config& c, double ms);
 // The winner for a filter size: the entry of `prefer` if cached, else the
 // most recent entry of any shape with that filter size. *from: its shape.
-int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
-                        const conv2d_shape& prefer, conv2d_config* c, conv2d_shape* from = nullptr);
+bool cache_lookup_filter(const Winners& w, int fh, int fw, const conv2d_shape& prefer, conv2d_config* c,
+                         conv2d_shape* from = nullptr);
 // Outputs below which that entry is preferred to the winner of the filter at
 // another size. The shipped entry has 128 x 16 outputs a workgroup: up to
 // about 8 waves per SIMD of it. Winners at 4096 x 4096 have larger tiles that

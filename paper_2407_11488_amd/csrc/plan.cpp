@@ -241,20 +241,17 @@ extern "C" int conv2d_plan(conv2d_plan_t* plan, conv2d_shape s, const conv2d_con
         p->cfg = *cfg;
         p->source = 2;
     } else {
-        double ms = 0;
-        std::string wp = env_str("CONV2D_WINNERS");
-        if (wp.empty()) wp = winners_default_path();
+        const Winners w = plan_winners(dev.arch);
         bool stale = false;
         conv2d_config own{}, near{};
         conv2d_shape from{};
-        const bool have_own = cache_lookup(wp, dev.arch, s, &own, &ms, &stale) == CONV2D_OK;
+        const bool have_own = cache_lookup(w, s, &own, nullptr, &stale);
         // The same filter's winner for another shape (4096 x 4096 first).
         const bool have_near = !have_own &&
-                               cache_lookup_filter(wp, dev.arch, s.filt_h, s.filt_w,
-                                                   conv2d_shape{4096, 4096, s.filt_h, s.filt_w}, &near,
-                                                   &from) == CONV2D_OK &&
+                               cache_lookup_filter(w, s.filt_h, s.filt_w,
+                                                   conv2d_shape{4096, 4096, s.filt_h, s.filt_w}, &near, &from) &&
                                conv2d_config_check(s, &near, dev.lds_limit) == CONV2D_OK;
-        const AnyShape a = have_own ? AnyShape{} : cache_lookup_any(wp, dev, s.filt_h, s.filt_w);
+        const AnyShape a = have_own ? AnyShape{} : cache_lookup_any(w, dev, s.filt_h, s.filt_w);
         const conv2d_config any = a.found ? a.pick(s) : conv2d_config{};
         bool gives_way = false;   // near to any
         if (have_near && a.found) {

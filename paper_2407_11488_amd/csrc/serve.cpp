@@ -147,6 +147,7 @@ public:
     {
         int rc = current_device_info(&dev_);
         if (rc) return rc;
+        winners_ = plan_winners(dev_.arch);
         req_.assign(n_, Req{});
         size_t max_tiles_per_req = 1;
         for (int i = 0; i < n_; ++i) {
@@ -167,8 +168,8 @@ public:
                 const auto bkey = std::make_tuple(s.filt_h, s.filt_w, size_bucket(s.out_h, s.out_w));
                 auto it = configs_of_bucket_.find(bkey);
                 if (it == configs_of_bucket_.end())
-                    it = configs_of_bucket_.emplace(bkey, batch_configs_for(dev_, s.filt_h, s.filt_w,
-                                                                            std::get<2>(bkey), 0)).first;
+                    it = configs_of_bucket_.emplace(bkey, batch_configs_for(winners_, dev_, s.filt_h,
+                                                                            s.filt_w, std::get<2>(bkey))).first;
                 const conv2d_config chosen = it->second.pick(s);
                 const auto ckey = std::make_pair(std::make_pair(s.filt_h, s.filt_w), config_str(chosen));
                 auto jt = kernel_of_cfg_.find(ckey);
@@ -436,11 +437,9 @@ private:
         const auto key = std::make_tuple(s.filt_h, s.filt_w, kVec, kVec);
         auto fit = direct_cfg_.find({s.filt_h, s.filt_w});
         if (fit == direct_cfg_.end()) {
-            std::string wp = env_str("CONV2D_WINNERS");
-            if (wp.empty()) wp = winners_default_path();
             conv2d_config c;
             const conv2d_shape tuned{4096, 4096, s.filt_h, s.filt_w};
-            if (cache_lookup_filter(wp, dev_.arch, s.filt_h, s.filt_w, tuned, &c) != CONV2D_OK ||
+            if (!cache_lookup_filter(winners_, s.filt_h, s.filt_w, tuned, &c) ||
                 conv2d_config_check(tuned, &c, dev_.lds_limit) != CONV2D_OK)
                 conv2d_default_config(&c);
             clear_error();
@@ -499,6 +498,7 @@ private:
     int n_;
     conv2d_serve_opts o_;
     DeviceInfo dev_;
+    Winners winners_;
     std::vector<Req> req_;
     std::vector<FilterKernel> kernels_;
     std::map<std::tuple<int, int, int>, BatchConfigs> configs_of_bucket_;

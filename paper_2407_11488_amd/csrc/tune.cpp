@@ -48,65 +48,72 @@ static bool json_config(const JsonObj& o, conv2d_config* c)
     return true;
 }
 
-// An entry tuned for the current kernel source wins; an entry for an older
-// source revision of the same (arch, shape) is used only when no current one
-// exists (every configuration is correct; it may no longer be the fastest).
-int cache_lookup(const std::string& path, const std::string& arch, const conv2d_shape& s,
-                 conv2d_config* c, double* ms, bool* stale)
+Winners load_winners(const std::string& path, const std::string& arch)
 {
+    Winners w;
     std::ifstream f(path);
-    if (!f) return fail(CONV2D_ENOTUNED, "no winners cache at " + path);
+    w.readable = (bool)f;
     const std::string src = hex64(direct_source_hash());
-    bool have_cur = false, have_old = false;
-    conv2d_config cur{}, old{};
-    double cur_ms = 0, old_ms = 0;
-    std::string line;
-    while (std::getline(f, line)) {
-        JsonObj o;
-        if (!json_parse_line(line, &o)) continue;
-        if (o.str["arch"] != arch || !json_shape_is(o, s)) continue;
-        conv2d_config cc;
-        if (!json_config(o, &cc)) continue;
-        if (o.str["src"] == src) { cur = cc; cur_ms = o.num["ms"]; have_cur = true; }
-        else { old = cc; old_ms = o.num["ms"]; have_old = true; }
-    }
-    if (!have_cur && !have_old) return fail(CONV2D_ENOTUNED, "shape not in winners cache");
-    if (c) *c = have_cur ? cur : old;
-    if (ms) *ms = have_cur ? cur_ms : old_ms;
-    if (stale) *stale = !have_cur;
-    return CONV2D_OK;
-}
-
-int cache_lookup_filter(const std::string& path, const std::string& arch, int fh, int fw,
-                        const conv2d_shape& prefer, conv2d_config* c, conv2d_shape* from)
-{
-    if (cache_lookup(path, arch, prefer, c, nullptr) == CONV2D_OK) {
-        if (from) *from = prefer;
-        return CONV2D_OK;
-    }
-    std::ifstream f(path);
-    if (!f) return fail(CONV2D_ENOTUNED, "no winners cache at " + path);
-    const std::string src = hex64(direct_source_hash());
-    bool have_cur = false, have_old = false;
-    conv2d_config cur{}, old{};
-    conv2d_shape cur_s{}, old_s{};
     std::string line;
     while (std::getline(f, line)) {
         JsonObj o;
         if (!json_parse_line(line, &o) || o.str["arch"] != arch) continue;
         auto it = o.arr.find("shape");
-        if (it == o.arr.end() || it->second.size() != 4 || (int)it->second[2] != fh || (int)it->second[3] != fw)
-            continue;
-        const conv2d_shape ss{(int)it->second[0], (int)it->second[1], fh, fw};
-        conv2d_config cc;
-        if (!json_config(o, &cc)) continue;
-        if (o.str["src"] == src) { cur = cc; cur_s = ss; have_cur = true; }
-        else { old = cc; old_s = ss; have_old = true; }
+        Winner e;
+        if (it == o.arr.end() || it->second.size() != 4 || !json_config(o, &e.config)) continue;
+        const auto& a = it->second;
+        e.shape = conv2d_shape{(int)a[0], (int)a[1], (int)a[2], (int)a[3]};
+        e.ms = o.num["ms"];
+        e.current = o.str["src"] == src;
+        w.all.push_back(e);
     }
-    if (!have_cur && !have_old) return fail(CONV2D_ENOTUNED, "filter size not in winners cache");
-    *c = have_cur ? cur : old;
-    if (from) *from = have_cur ? cur_s : old_s;
-    return CONV2D_OK;
+    return w;
+}
+
+Winners plan_winners(const std::string& arch)
+{
+    const std::string path = env_str("CONV2D_WINNERS");
+    return load_winners(path.empty() ? winners_default_path() : path, arch);
+}
+
+// The last entry that fits, one tuned for the current kernel source before
+// those of older revisions (every configuration is correct; an old one may no
+// longer be the fastest).
+template <class Fits>
+static const Winner* last_winner(const Winners& w, Fits fits)
+{
+    const Winner *cur = nullptr, *old = nullptr;
+    for (const auto& e : w.all)
+        if (fits(e)) (e.current ? cur : old) = &e;
+    return cur ? cur : old;
+}
+
+bool cache_lookup(const Winners& w, const conv2d_shape& s, conv2d_config* c, double* ms, bool* stale)
+{
+    const Winner* e = last_winner(w, [&](const Winner& x) {
+        return x.shape.out_h == s.out_h && x.shape.out_w == s.out_w && x.shape.filt_h == s.filt_h &&
+               x.shape.filt_w == s.filt_w;
+    });
+    if (!e) return false;
+    if (c) *c = e->config;
+    if (ms) *ms = e->ms;
+    if (stale) *stale = !e->current;
+    return true;
+}
+
+bool cache_lookup_filter(const Winners& w, int fh, int fw, const conv2d_shape& prefer, conv2d_config* c,
+                         conv2d_shape* from)
+{
+    if (cache_lookup(w, prefer, c)) {
+        if (from) *from = prefer;
+        return true;
+    }
+    const Winner* e =
+        last_winner(w, [&](const Winner& x) { return x.shape.filt_h == fh && x.shape.filt_w == fw; });
+    if (!e) return false;
+    *c = e->config;
+    if (from) *from = e->shape;
+    return true;
 }
 
 // Plain entries by their outputs, the batched path's (0, bucket, ..) by the
@@ -116,14 +123,12 @@ bool tuned_small(const conv2d_shape& e)
     return e.out_h == 0 ? e.out_w <= 3 : (long long)e.out_h * e.out_w < kSmallOutputs;
 }
 
-AnyShape cache_lookup_any(const std::string& path, const DeviceInfo& dev, int fh, int fw)
+AnyShape cache_lookup_any(const Winners& w, const DeviceInfo& dev, int fh, int fw)
 {
     AnyShape r;
     const conv2d_shape s{4096, 4096, fh, fw};
     conv2d_config any{};
-    if (cache_lookup(path, dev.arch, kAnyShape, &any, nullptr) != CONV2D_OK ||
-        conv2d_config_check(s, &any, dev.lds_limit) != CONV2D_OK)
-        return r;
+    if (!cache_lookup(w, kAnyShape, &any) || conv2d_config_check(s, &any, dev.lds_limit) != CONV2D_OK) return r;
     r.found = true;
     r.configs = {any, {16, 16, 2, 2, 1, 0, 4}, {128, 2, 4, 1, 0, 0, 4}, {128, 2, 4, 2, 1, 0, 4},
                  {64, 4, 4, 2, 1, 0, 4}};
@@ -873,7 +878,11 @@ extern "C" int conv2d_cache_lookup(const char* path, const char* arch, conv2d_sh
         if (rc) return rc;
         a = d.arch;
     }
-    return cache_lookup(path ? path : winners_default_path(), a, s, cfg, ms);
+    const std::string file = path ? path : winners_default_path();
+    const Winners w = load_winners(file, a);
+    if (!w.readable) return fail(CONV2D_ENOTUNED, "no winners cache at " + file);
+    if (!cache_lookup(w, s, cfg, ms)) return fail(CONV2D_ENOTUNED, "shape not in winners cache");
+    return CONV2D_OK;
 }
 
 extern "C" int conv2d_cache_store(const char* path, const char* arch, conv2d_shape s, const conv2d_config* cfg,

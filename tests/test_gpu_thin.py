@@ -65,13 +65,18 @@ def test_large_thin_images_of_a_tuned_filter(tmp_path, monkeypatch):
         plan.close()
 
 
-def test_thin_images_in_batches():
+# (images, configurations by size, configuration of a plain batch): an image gets
+# a kernel of its own by size where its shape saves more than a launch, 5 us
+@pytest.mark.parametrize("shapes,by_size,plain", [
+    ([(9000, 20), (200, 300), (2, 9000), (4000, 9), (12000, 33)], {NARROW, ANY}, NARROW),
+    ([(300, 20), (200, 300), (2, 900), (400, 9)], {ANY}, NARROW),
+    ([(1, 900000), (2, 900000)], {TWO, TWO_LARGE}, TWO)])
+def test_thin_images_in_batches(shapes, by_size, plain):
     torch = torch_cuda()
-    shapes = [(300, 20, 11, 11), (200, 300, 11, 11), (2, 900, 11, 11), (400, 9, 11, 11), (500, 33, 11, 11)]
+    shapes = [s + (11, 11) for s in shapes]
     probs = [datagen.conv_problem(*s, kind="int", seed_in=k + 1, seed_f=k + 9) for k, s in enumerate(shapes)]
     refs = [oracle.conv2d_f64(i, f)[0] for i, f in probs]
-    by_size = {NARROW, ANY, TWO_LARGE}
-    for flags, want in ((C.CONV2D_BATCH_BY_SIZE, by_size), (0, {NARROW})):
+    for flags, want in ((C.CONV2D_BATCH_BY_SIZE, by_size), (0, {plain})):
         b = C.Batch(shapes, flags)
         say(f"thin batch flags {flags}: {b.info['groups']}")
         assert {tuple(g["config"]) for g in b.info["groups"]} == want
