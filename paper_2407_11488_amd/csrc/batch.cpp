@@ -300,9 +300,10 @@ extern "C" int conv2d_batch_plan(conv2d_batch_t* out, int n, const conv2d_shape*
     // share a configuration share a kernel).
     // An image that its entry covers badly (BatchConfigs::pick) gets a kernel of
     // its own by size, if other images have it anyway or if those that share it
-    // save more than one more kernel costs: its launch and about the run of one tile, 3 us at 3 x 3 and 13 at 31
-    // x 31 (200 images up to 200 under 31 x 31, 7 us saved: 56 us with one kernel,
-    // 76 with two).
+    // save more than one more kernel costs: its launch and about the run of one
+    // tile, taken as 5 us at 3 x 3 and 15 at 31 x 31 (200 images up to 200 under
+    // 31 x 31, 7 us saved: 56 us with one kernel, 76 with two; 16 images up to
+    // 768: 24.7 us with four kernels, 29.2 with a fifth for a few of them).
     const Winners winners = plan_winners(b->dev.arch);
     const bool by_size = (flags & CONV2D_BATCH_BY_SIZE) != 0;
     using Key = std::pair<std::pair<int, int>, std::string>;
